@@ -1,5 +1,6 @@
 // Code search by beam search (Appendix C, code optimisation; Alg. 1 updates the assignments b by
-// beam search), for codebooks of 256 (8-bit codes) or 16 (4-bit codes) codewords: for every group
+// beam search), for codebooks of 16 codewords (4-bit codes), and of 256 (8-bit codes) at beams above
+// 8 (up to 8 they go to k_beam_mma.hip, which takes the decisions stated here): for every group
 // (row i, group j) of a dense weight matrix, the tuple
 // (c_0, ..., c_{k-1}) of codewords of codebooks 0..k-1 that minimises the group's squared error
 // ||w - s_i sum_m C_m[c_m]||^2 is searched stage by stage, keeping the `beam` best partial tuples.
@@ -418,13 +419,15 @@ template <int B>
 static hipError_t launch_beam_weighted_b(const BeamWeightedArgs& a, int ncw, hipStream_t st) {
   const int grid = ((a.d_out + beam::kThreads - 1) / beam::kThreads) * a.G;   // validated below 2^31
   if (ncw == 16) beam_weighted_kernel<B, 16><<<grid, beam::kThreads, (size_t)a.k * 16 * 16, st>>>(a);
-  else beam_weighted_kernel<B, 256><<<grid, beam::kThreads, (size_t)a.k * 256 * 16, st>>>(a);
+  else if constexpr (B > 8) beam_weighted_kernel<B, 256><<<grid, beam::kThreads, (size_t)a.k * 256 * 16, st>>>(a);
   return hipGetLastError();
 }
 
 hipError_t launch_beam_search_weighted(const aqmb_desc& d, int k, int beam_width, const void* W,
                                        const uint16_t* codebooks, const uint16_t* scales, const float* H,
                                        unsigned char* codes, float* errors, hipStream_t st) {
+  if (d.code_bits == 8 && beam_width <= 8)          // as in launch_beam_search
+    return launch_beam_mma(d, k, beam_width, W, codebooks, scales, H, codes, errors, st);
   BeamWeightedArgs a{};
   a.W = (const uint16_t*)W;
   a.codebooks = codebooks;
@@ -461,12 +464,17 @@ template <int B>
 static hipError_t launch_beam_b(const BeamArgs& a, int ncw, hipStream_t st) {
   const int grid = ((a.G + beam::kThreads - 1) / beam::kThreads) * a.d_out;   // validated below 2^31
   if (ncw == 16) beam_kernel<B, 16><<<grid, beam::kThreads, (size_t)a.k * 16 * 16, st>>>(a);
-  else beam_kernel<B, 256><<<grid, beam::kThreads, (size_t)a.k * 256 * 16, st>>>(a);
+  else if constexpr (B > 8) beam_kernel<B, 256><<<grid, beam::kThreads, (size_t)a.k * 256 * 16, st>>>(a);
   return hipGetLastError();
 }
 
 hipError_t launch_beam_search(const aqmb_desc& d, int k, int beam_width, const void* W, const uint16_t* codebooks,
                               const uint16_t* scales, unsigned char* codes, float* errors, hipStream_t st) {
+  // 256-codeword books and beams of at most 8 go to the matrix-core filter (same results, 4096 x 4096,
+  // k = 4, beam 8: 11.3 -> 2.48 ms). Wider beams stay here: their kept tuples would take two passes of
+  // its registers; 16-codeword books too: a stage has only 16 candidates per kept tuple.
+  if (d.code_bits == 8 && beam_width <= 8)
+    return launch_beam_mma(d, k, beam_width, W, codebooks, scales, nullptr, codes, errors, st);
   BeamArgs a{};
   a.W = (const uint16_t*)W;
   a.codebooks = codebooks;

@@ -51,6 +51,10 @@ hipError_t launch_beam_search(const aqmb_desc& d, int k, int beam_width, const v
 hipError_t launch_beam_search_weighted(const aqmb_desc& d, int k, int beam_width, const void* W,
                                        const uint16_t* codebooks, const uint16_t* scales, const float* H,
                                        unsigned char* codes, float* errors, hipStream_t st);
+// Both searches for 8-bit codes and beams of at most 8 (H null: the plain objective), the matrix cores
+// as a filter; the same codes and errors bit for bit.
+hipError_t launch_beam_mma(const aqmb_desc& d, int k, int beam_width, const void* W, const uint16_t* codebooks,
+                           const uint16_t* scales, const float* H, unsigned char* codes, float* errors, hipStream_t st);
 // Prefill GEMM tiled for small token counts (same arithmetic as launch_gemm).
 hipError_t launch_gemm_small(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                              hipStream_t st);
