@@ -21,7 +21,7 @@ LIB = os.path.join(HERE, "libaqmb.so")
 CEIL_SOURCES = ["ceilings.hip"]
 CEIL_LIB = os.path.join(HERE, "libaqmb_ceilings.so")
 
-SOURCES = ["validate.cpp", "api.cpp", "k_dequant.hip", "k_gemv.hip", "k_gemv16.hip", "k_gemv4.hip", "k_gemv_mma.hip", "k_gemm.hip", "k_gemm_small.hip", "k_distortion.hip", "k_beam.hip", "k_beam_mma.hip"]
+SOURCES = ["validate.cpp", "api.cpp", "k_dequant.hip", "k_gemv.hip", "k_gemv16.hip", "k_gemv4.hip", "k_gemv_mma.hip", "k_gemm.hip", "k_gemm_small.hip", "k_gemm_mid.hip", "k_distortion.hip", "k_beam.hip", "k_beam_mma.hip"]
 ARCH = "gfx950"
 
 

@@ -208,9 +208,19 @@ static aqmb_status launch_gemv_kernel(const Layer& L, int k, const void* x, aqmb
   return e == hipSuccess ? AQMB_OK : hip_fail(e, where);
 }
 
-// GEMM tiling: small token counts take the 16-row tiling (every CU busy), larger ones the
-// large-tile kernel with the tile shape that needs the fewest rounds of workgroups.
+// GEMM kernel choice (AQMB_GEMM_AUTO). From 17 tokens and up to k = 4 the split-input kernel
+// (k_gemm_mid.hip) where its estimated time is at least 5 % below the large tiles' (4096 x 4096, k = 4,
+// large tiles or 16-row tiling against it: 23.0 / 13.3 us at 64 tokens, 52.1 / 20.1 at 150, 76.1 / 61.1
+// at 1024, 89.6 / 91.3 at 1500, where the large tiles stay), and never where aqmb_gemm_ws has a
+// two-pass path: that is bit-identical to the 256 x 128 tiling. Otherwise small token counts take the
+// 16-row tiling (every CU busy), larger ones the large-tile kernel with the tile shape that needs the
+// fewest rounds of workgroups.
 constexpr int kGemmSmallMax = 144;   // tokens: the 16-row tiling re-gathers per 64 tokens; measured break-even with 128 x 64 tiles near 150
+static bool gemm_takes_mid(const Layer& L, int k, int n_tokens) {
+  if (n_tokens <= 16 || gemm_two_pass_bytes(L, k, n_tokens) != 0) return false;
+  const double mid = gemm_mid_us(L, k, n_tokens);
+  return mid >= 0 && mid < 0.95 * gemm_large_us(L, k, n_tokens);
+}
 
 // k must name resident planes.
 static aqmb_status check_resident(const Layer* L, int k, const char* where) {
@@ -417,6 +427,10 @@ static aqmb_status gemm_impl(aqmb_layer_t layer, int k, const void* X, int n_tok
   if ((s = check_device(L)) != AQMB_OK) return s;
   const bool small = tiling == AQMB_GEMM_ROWS16 || (tiling == AQMB_GEMM_AUTO && n_tokens <= kGemmSmallMax);
   const int tile = tiling == AQMB_GEMM_256x128 ? 0 : tiling == AQMB_GEMM_128x128 ? 1 : tiling == AQMB_GEMM_128x64 ? 2 : -1;
+  if (tiling == AQMB_GEMM_AUTO && gemm_takes_mid(*L, k, n_tokens)) {
+    const hipError_t em = launch_gemm_mid(*L, k, X, n_tokens, Y, y_dtype, (hipStream_t)stream);
+    return em == hipSuccess ? AQMB_OK : hip_fail(em, where);
+  }
   hipError_t e = small ? launch_gemm_small(*L, k, X, n_tokens, Y, y_dtype, (hipStream_t)stream)
                        : launch_gemm(*L, k, X, n_tokens, Y, y_dtype, tile, (hipStream_t)stream);
   return e == hipSuccess ? AQMB_OK : hip_fail(e, where);

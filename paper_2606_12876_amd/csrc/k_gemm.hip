@@ -551,6 +551,19 @@ static int gemm_tile(const Layer& L, int n_tokens, int forced) {
   return best;
 }
 
+// One round of 256 workgroups measured on a 4096-input layer (k = 1..4, us), the part above 5 us in
+// proportion to d_in; a last round that is not full counts 0.7 (11008 x 4096, 900 tokens, 1.34 rounds
+// of 256 x 128: 165 us at k = 4, 128 us at k = 1).
+double gemm_large_us(const Layer& L, int k, int n_tokens) {
+  static const double us[3][4] = {{72.0, 77.5, 86.6, 96.8}, {52.0, 60.0, 68.0, 77.0}, {36.0, 41.0, 47.0, 53.0}};
+  const int bm[3] = {256, 128, 128}, bn[3] = {128, 128, 64};
+  const int c = gemm_tile(L, n_tokens, -1);
+  const long long ncu = L.n_cu > 0 ? L.n_cu : 256;
+  const long long wg = (long long)((n_tokens + bm[c] - 1) / bm[c]) * ((L.d.d_out + bn[c] - 1) / bn[c]);
+  const double rounds = wg <= ncu ? 1.0 : (double)(wg / ncu) + (wg % ncu ? 0.7 : 0.0);
+  return rounds * (5.0 + (us[c][k - 1] - 5.0) * L.d.d_in / 4096.0);
+}
+
 template <int K, int CB>
 static void launch_kc(const Layer& L, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, int tile,
                       hipStream_t st) {

@@ -58,10 +58,17 @@ hipError_t launch_beam_mma(const aqmb_desc& d, int k, int beam_width, const void
 // Prefill GEMM tiled for small token counts (same arithmetic as launch_gemm).
 hipError_t launch_gemm_small(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                              hipStream_t st);
+// Prefill GEMM for tens to hundreds of tokens, k <= 4 (same arithmetic).
+// gemm_mid_us: its estimated time (-1 where it does not serve the call).
+double gemm_mid_us(const Layer& L, int k, int n_tokens);
+hipError_t launch_gemm_mid(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
+                           hipStream_t st);
 // Large-tile prefill GEMM; tile: -1 = chosen by the number of workgroup rounds, 0 = 256 x 128,
 // 1 = 128 x 128, 2 = 128 x 64 (tokens x weight rows).
 hipError_t launch_gemm(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, int tile,
                        hipStream_t st);
+// Estimated time of launch_gemm's choice of tile, k <= 4.
+double gemm_large_us(const Layer& L, int k, int n_tokens);
 // Two-pass prefill GEMM (bit-identical to the 256 x 128 tiling): workspace bytes (0 where it does
 // not apply) and the launch (workspace of at least that many bytes, 256-byte aligned).
 size_t gemm_two_pass_bytes(const Layer& L, int k, int n_tokens);
