@@ -329,11 +329,6 @@ __device__ __forceinline__ float group_dot_acc(uint4 xw, uint4 cw, float s) {
 // cw_convert_own_bf16 to x / scl[group] (scl rows of rstride / 16 floats). A group's dot products
 // are chained over the planes into one partial sum (independent chains, one v_dot2 per code word
 // pair), which is then added to the row's accumulator (XS: multiplied by the group's scale).
-// `after_gathers` runs in each wave once its own gathers are done, before the row reduction's
-// barrier (the multi-layer kernel writes the next layer's replicas there).
-struct CwNothing {
-  __device__ void operator()() const {}
-};
 // x of a thread's 8 groups (and, for bf16 x, their scales) held in registers by kernels that run
 // several row blocks or layers on one x (one batch row, rows of one 512-group block), so that the
 // staged x is read from LDS once per workgroup instead of once per block.
@@ -350,12 +345,12 @@ __device__ __forceinline__ void cw_load_xreg(const uint16_t* xs, const float* sc
 #pragma unroll
   for (int jj = 0; jj < 8; ++jj) xr.s[jj] = XS && ok ? scl[j0 + jj] : 0.f;
 }
-template <int K, int NB, int UB, bool XS, bool PL, bool XR = false, typename After = CwNothing>
+template <int K, int NB, int UB, bool XS, bool PL, bool XR = false>
 __device__ __forceinline__ void cw_tile(const uint2 (&code)[UB][K], const uint4* cb_rep, const uint16_t* xs,
                                         size_t rstride, int Gp, int cb_shift, uint32_t rep_off,
                                         float (&red)[cw::kWaves][cw::kRows][NB], int b0, int batch, int row,
                                         bool row_ok, float scale, void* y, int d_out, int y_dtype,
-                                        const float* scl, const CwXReg& xr, const After& after_gathers = After()) {
+                                        const float* scl, const CwXReg& xr) {
   static_assert(!XR || (NB == 1 && UB == 1), "x in registers: one batch row, one block per row");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -490,7 +485,6 @@ __device__ __forceinline__ void cw_tile(const uint2 (&code)[UB][K], const uint4*
       }
     }
   }
-  after_gathers();
   // row sum: lanes rw, rw + 16, rw + 32, rw + 48 of the wave, then the 16 waves in order
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
@@ -782,15 +776,8 @@ void gemv_cw_persist_kernel(GemvArgs a) {
 }
 
 // ------------------------------------------------------------------ several layers, one launch
-// Layers that share the input x (fused projections such as q/k/v or gate/up): one persistent
-// workgroup per 16-row block walks through the layers that have that block. x is staged once;
-// the replicas of the next layer's codebooks are written right after the reduction barrier of
-// the current one (every wave has finished its gathers by then; wave 0 still reads only the row
-// sums), and one more barrier publishes them;
-// while a layer's codewords are gathered, the codebook word and code words of the next layer are
-// already on their way (two register sets used in turn), so a layer costs its gathers and the
-// replica writes of its codebooks, not a launch and the load latency. Results are those of one
-// aqmb_gemv call per layer (same arithmetic, same reduction order).
+// Layers that share the input x (fused projections such as q/k/v or gate/up), batch 1. Results are
+// those of one aqmb_gemv call per layer (same arithmetic, same reduction order).
 struct GemvMultiLayer {
   const unsigned char* codes;
   const uint16_t* codebooks;
@@ -799,120 +786,98 @@ struct GemvMultiLayer {
   size_t plane_bytes;
   int d_out;
   int row_blocks;                                          // ceil(d_out / 16)
+  int first;                                               // row blocks of the layers before this one
 };
 
 struct GemvMultiArgs {
   GemvMultiLayer L[AQMB_MAX_MULTI];
   const void* x;
   const void* zero_page;
-  int n_layers, d_in, S, batch, y_dtype, nrep, cb_shift;
+  int n_layers, total, d_in, S, y_dtype, nrep, cb_shift;  // total: row blocks of all layers
 };
 
-template <int K, int NB, int XDT, int UB, bool DB, bool PL>
+// The row blocks of all layers form one sequence, layer after layer, and a persistent workgroup per
+// compute unit takes an even, contiguous range of it: most workgroups stay within one layer, so x is
+// staged and (mostly) the codebooks are replicated once per workgroup, and the last round of blocks
+// is shared out over the whole call instead of per layer. While a block's codewords are gathered, the
+// next block's codebook word, row scale and code words are on their way (two register sets); where
+// the next block belongs to another layer, its replicas are written right after the reduction barrier
+// of the current block (every wave has finished its gathers by then) and one more barrier publishes
+// them. Row sums alternate between two buffers, so that no barrier is needed between blocks of one
+// layer. UB = 512-group blocks per row (x in registers for every block at UB = 1).
+// Measured, batch 1, bf16 x, against a workgroup per row block walking through the layers, which
+// replicated the codebooks at every layer: see launch_gemv_multi.
+template <int K, int XDT, int UB, bool PL>
 __global__ __launch_bounds__(cw::kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void gemv_cw_multi_kernel(GemvMultiArgs a) {
+  constexpr int NB = 1;
+  constexpr bool kXR = UB == 1, kXS = XDT == AQMB_BF16;    // bf16 x: converted to fp16 per group, once
   extern __shared__ uint4 smem_cw[];
   const int nrep = a.nrep;
-  // DB: two replica sets (and two row-sum buffers) in turn. Each wave writes the next layer's
-  // replicas into the idle set as soon as its own gathers of the current layer are done; the
-  // row reduction's barrier then separates those writes from the next layer's gathers, and no
-  // barrier of its own is needed. A set (or buffer) is written again two layers later, after a
-  // barrier that every wave reaches only once it has finished reading it.
-  const int rep_words = cw_rep_words<K, PL>(nrep);
-  uint4* rep[2] = {smem_cw, smem_cw + (DB ? rep_words : 0)};
-  uint16_t* xs = (uint16_t*)(smem_cw + (DB ? 2 : 1) * rep_words);
+  uint4* rep = smem_cw;
+  uint16_t* xs = (uint16_t*)(smem_cw + cw_rep_words<K, PL>(nrep));
   const int tid = threadIdx.x, lane = tid & 63;
   const int rw = lane & 15;
-  const int row = blockIdx.x * cw::kRows + rw;
   const int Gp = a.S * 16;
   const size_t rstride = cw::row_stride(a.S);
   const uint32_t xs_base = lds_addr(xs);
   const uint32_t rep_off = (uint32_t)(lane % nrep) * 16;
-  // next layer (after l) that has this workgroup's row block, or -1 (uniform)
-  auto next_layer = [&](int l) {
-    for (int j = l + 1; j < a.n_layers; ++j)
-      if ((int)blockIdx.x < a.L[j].row_blocks) return j;
-    return -1;
-  };
-  // the layer's codebook word (first) and row scale; its code words
-  auto load_small = [&](int l, uint4& cbv, uint32_t& sbits) {
-    cbv = cw_first_word<K, PL>(a.L[l].codebooks);
-    asm volatile("" ::: "memory");                        // the codebook word goes out first
-    const int d_out = a.L[l].d_out;
-    sbits = a.L[l].scales[row < d_out ? row : d_out - 1];
-  };
-  auto load_codes = [&](int l, uint2 (&code)[UB][K]) {
-    const int d_out = a.L[l].d_out;
-    cw_load_codes<K, UB>(code, a.L[l].codes, a.L[l].plane_bytes, d_out, row < d_out ? row : d_out - 1, Gp);
-  };
-  // the layer's codebook word (first), row scale and code words
-  auto load_layer = [&](int l, uint4& cbv, uint32_t& sbits, uint2 (&code)[UB][K]) {
-    load_small(l, cbv, sbits);
-    load_codes(l, code);
-  };
-  constexpr bool kXS = XDT == AQMB_BF16;                   // bf16 x: converted to fp16 per group, once
-  float* scl = (float*)((char*)xs + NB * rstride);         // [NB][rstride / 16] group scales
-  float (&red)[DB ? 2 : 1][cw::kWaves][cw::kRows][NB] = cw_red<NB, DB ? 2 : 1>(scl, rstride, kXS);   // row sums
-  int buf = 0;                                             // the replica set and row-sum buffer in use
-  // batch 1: x of this thread's groups in registers for every layer (not with bf16 x at k = 2 in
-  // two paired replica sets, where they would not fit)
-  constexpr bool kXR = NB == 1 && UB == 1 && !(XDT == AQMB_BF16 && K == 2 && DB && PL);
+  float* scl = (float*)((char*)xs + rstride);              // [rstride / 16] group scales
+  float (&red)[2][cw::kWaves][cw::kRows][NB] = cw_red<NB, 2>(scl, rstride, kXS);   // row sums
   CwXReg xr;
-  // layer l from replica set `buf`; with DB and a next layer, its replicas (word cbn) go to the
-  // other set once this wave's gathers are done
-  auto run_layer = [&](int l, uint32_t sbits, const uint2 (&code)[UB][K], bool next, const uint4& cbn) {
-    const int d_out = a.L[l].d_out;
-    auto after = [&]() {
-      if constexpr (DB) {
-        if (next) {
-          wait_vmcnt<UB * K + 1>();                        // the next codebook word is in
-          cw_replicate_any<K, PL>(rep[buf ^ 1], cbn, nrep, a.cb_shift);
-        }
-      }
-    };
-    cw_tile<K, NB, UB, kXS, PL, kXR>(code, rep[buf], xs, rstride, Gp, a.cb_shift, rep_off,
-                                                    red[DB ? buf : 0], 0, a.batch, row, row < d_out,
-                                                    f16_to_f32((uint16_t)sbits), a.L[l].y, d_out, a.y_dtype, scl, xr,
-                                                    after);
+  // block `it` of the sequence: its codebook word (first), row scale and code words
+  auto load = [&](int l, int it, uint4& cbv, uint32_t& sbits, uint2 (&code)[UB][K], bool first) {
+    const int d_out = a.L[l].d_out, row = (it - a.L[l].first) * cw::kRows + rw;
+    const int rowc = row < d_out ? row : d_out - 1;
+    cbv = cw_first_word<K, PL>(a.L[l].codebooks);
+    asm volatile("" ::: "memory");                         // the codebook word goes out first
+    sbits = a.L[l].scales[rowc];
+    if (first) cw_small_loads_first();
+    cw_load_codes<K, UB>(code, a.L[l].codes, a.L[l].plane_bytes, d_out, rowc, Gp);
   };
-  // after layer `cur` (its reduction barrier passed): make `nxt` current
-  auto switch_to = [&](const uint4& cbn) {
-    if constexpr (DB) {
-      buf ^= 1;
-    } else {
-      wait_vmcnt<UB * K + 1>();                            // the next codebook word is in
-      cw_replicate_any<K, PL>(rep[0], cbn, nrep, a.cb_shift);
-      __syncthreads();
-    }
+  auto run = [&](int l, int it, int buf, uint32_t sbits, const uint2 (&code)[UB][K]) {
+    const int d_out = a.L[l].d_out, row = (it - a.L[l].first) * cw::kRows + rw;
+    cw_tile<K, NB, UB, kXS, PL, kXR>(code, rep, xs, rstride, Gp, a.cb_shift, rep_off, red[buf], 0, 1, row, row < d_out,
+                                     f16_to_f32((uint16_t)sbits), a.L[l].y, d_out, a.y_dtype, scl, xr);
+  };
+  auto layer_at = [&](int l, int it) { while (it >= a.L[l].first + a.L[l].row_blocks) ++l; return l; };
+  auto to_layer = [&](const uint4& cbn) {                  // after a block's reduction barrier
+    wait_vmcnt<UB * K + 1>();                              // the codebook word is in
+    cw_replicate_any<K, PL>(rep, cbn, nrep, a.cb_shift);
+    __syncthreads();
   };
 
-  int cur = next_layer(-1);                                // the grid never exceeds the largest layer
-  cw_stage_x<NB>(a.x, a.zero_page, 0, a.batch, a.d_in, rstride, xs_base);
+  const int end = (int)(((long long)(blockIdx.x + 1) * a.total) / gridDim.x);
+  int it = (int)(((long long)blockIdx.x * a.total) / gridDim.x);   // the grid never exceeds the block count
+  int l = layer_at(0, it);
+  cw_stage_x<NB>(a.x, a.zero_page, 0, 1, a.d_in, rstride, xs_base);
   asm volatile("" ::: "memory");
   uint4 cba, cbb;
   uint32_t sa, sb;
   uint2 ca[UB][K], cb[UB][K];
-  load_small(cur, cba, sa);
-  cw_small_loads_first();
-  load_codes(cur, ca);
+  load(l, it, cba, sa, ca, true);
   wait_vmcnt<UB * K + 1>();                                // x and the codebook word are in
   if constexpr (kXS) cw_convert_own_bf16<NB>(xs, scl, rstride);
-  cw_replicate_any<K, PL>(rep[0], cba, nrep, a.cb_shift);
+  cw_replicate_any<K, PL>(rep, cba, nrep, a.cb_shift);
   __syncthreads();
   if constexpr (kXR) cw_load_xreg<kXS>(xs, scl, Gp, xr);
   for (;;) {
-    int nxt = next_layer(cur);
-    load_layer(nxt >= 0 ? nxt : cur, cbb, sb, cb);         // without a next layer: a harmless reload
-    run_layer(cur, sa, ca, nxt >= 0, cbb);                 // its reduction barrier: all gathers done
-    if (nxt < 0) break;
-    switch_to(cbb);
-    cur = nxt;
-    nxt = next_layer(cur);
-    load_layer(nxt >= 0 ? nxt : cur, cba, sa, ca);
-    run_layer(cur, sb, cb, nxt >= 0, cba);
-    if (nxt < 0) break;
-    switch_to(cba);
-    cur = nxt;
+    int nx = it + 1 < end ? it + 1 : it;                   // past the last block: a harmless reload
+    int nl = layer_at(l, nx);
+    load(nl, nx, cbb, sb, cb, false);
+    run(l, it, 0, sa, ca);
+    if (nx == it) break;
+    if (nl != l) to_layer(cbb);
+    it = nx;
+    l = nl;
+    nx = it + 1 < end ? it + 1 : it;
+    nl = layer_at(l, nx);
+    load(nl, nx, cba, sa, ca, false);
+    run(l, it, 1, sb, cb);
+    if (nx == it) break;
+    if (nl != l) to_layer(cba);
+    it = nx;
+    l = nl;
   }
 }
 
@@ -1074,73 +1039,43 @@ hipError_t launch_gemv_lut(const Layer& L, int k, const void* x, aqmb_dtype x_dt
   return hipGetLastError();
 }
 
-template <int K, int NB, int XDT>
-static hipError_t launch_multi_nb(GemvMultiArgs a, int grid, hipStream_t st) {
-  a.nrep = cw_nrep(K, NB, a.S, XDT == AQMB_BF16);
+template <int K, int XDT, int UB>
+static hipError_t launch_multi_ub(GemvMultiArgs a, int grid, hipStream_t st) {
+  constexpr bool bf = XDT == AQMB_BF16;
+  // the layouts of the single-layer persistent kernel (both give identical results)
+  const size_t paired = cw_lds_paired(K, a.S, bf);
+  if constexpr (UB == 1 && K >= 2) {
+    if (paired <= cw_budget(1, 2)) {
+      a.nrep = 8;                                          // (a paired region holds 8 copies of each plane)
+      a.cb_shift = cw_shift(a.nrep);
+      gemv_cw_multi_kernel<K, XDT, UB, true><<<grid, cw::kThreads, paired + cw_red_bytes(1, 2), st>>>(a);
+      return hipGetLastError();
+    }
+  }
+  a.nrep = cw_nrep(K, 1, a.S, bf);
   a.cb_shift = cw_shift(a.nrep);
-  const size_t lds = cw_lds(K, NB, a.S, a.nrep, XDT == AQMB_BF16);
-  // two replica sets when they fit (k <= 2, one 512-group block, rows of at most 512 groups)
-  const size_t lds2 = lds + (size_t)K * 256 * a.nrep * 16;
-  const size_t budget = 160 * 1024 - (size_t)2 * cw::kWaves * cw::kRows * 4 * NB - 512;
-  // the paired layout at even k, where it fits (16 layers of 4096 x 4096 per launch, k = 2:
-  // 2.40 -> 2.11 us per layer, k = 4: 3.99 -> 3.75 us); at odd k the lone plane's 16 copies cost
-  // more replica writes per layer than its conflict-free gathers save (k = 1: 1.62 -> 2.28 us;
-  // k = 3: 3.15 -> 3.72 us). Both layouts give identical results.
-  if constexpr (NB == 1 && K % 2 == 0) {
-    const bool bf = XDT == AQMB_BF16;
-    if constexpr (K <= 2) {
-      const size_t p2 = cw_lds_paired(K, a.S, bf, 2);
-      if (cw_blocks(a.S) == 1 && p2 <= cw_budget(NB, 2)) {
-        gemv_cw_multi_kernel<K, NB, XDT, 1, true, true><<<grid, cw::kThreads, p2 + cw_red_bytes(NB, 2), st>>>(a);
-        return hipGetLastError();
-      }
-    }
-    const size_t p1 = cw_lds_paired(K, a.S, bf);
-    if (p1 <= cw_budget(NB)) {
-      if (cw_blocks(a.S) == 1) gemv_cw_multi_kernel<K, NB, XDT, 1, false, true><<<grid, cw::kThreads, p1 + cw_red_bytes(NB), st>>>(a);
-      else gemv_cw_multi_kernel<K, NB, XDT, kCwMaxBlocks, false, true><<<grid, cw::kThreads, p1 + cw_red_bytes(NB), st>>>(a);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (K <= 2) {
-    if (cw_blocks(a.S) == 1 && lds2 <= budget) {
-      gemv_cw_multi_kernel<K, NB, XDT, 1, true, false><<<grid, cw::kThreads, lds2 + cw_red_bytes(NB, 2), st>>>(a);
-      return hipGetLastError();
-    }
-  }
-  if (cw_blocks(a.S) == 1) {
-    gemv_cw_multi_kernel<K, NB, XDT, 1, false, false><<<grid, cw::kThreads, lds + cw_red_bytes(NB), st>>>(a);
-  } else {
-    gemv_cw_multi_kernel<K, NB, XDT, kCwMaxBlocks, false, false><<<grid, cw::kThreads, lds + cw_red_bytes(NB), st>>>(a);
-  }
+  gemv_cw_multi_kernel<K, XDT, UB, false><<<grid, cw::kThreads, cw_lds(K, 1, a.S, a.nrep, bf) + cw_red_bytes(1, 2), st>>>(a);
   return hipGetLastError();
-}
-
-template <int K, int XDT>
-static hipError_t launch_multi_k(const GemvMultiArgs& a, int grid, hipStream_t st) {
-  if (a.batch == 1) return launch_multi_nb<K, 1, XDT>(a, grid, st);
-  if (a.batch == 2) return launch_multi_nb<K, 2, XDT>(a, grid, st);
-  return launch_multi_nb<K, 4, XDT>(a, grid, st);  // batch 3..4: one tile of 4 rows
 }
 
 template <int XDT>
 static hipError_t launch_multi_x(const GemvMultiArgs& a, int k, int grid, hipStream_t st) {
+  if (cw_blocks(a.S) > 1) return launch_multi_ub<1, XDT, kCwMaxBlocks>(a, grid, st);   // k = 1 checked by the caller
   switch (k) {
-    case 1: return launch_multi_k<1, XDT>(a, grid, st);
-    case 2: return launch_multi_k<2, XDT>(a, grid, st);
-    case 3: return launch_multi_k<3, XDT>(a, grid, st);
-    default: return launch_multi_k<4, XDT>(a, grid, st);   // k <= 4 checked by the caller
+    case 1: return launch_multi_ub<1, XDT, 1>(a, grid, st);
+    case 2: return launch_multi_ub<2, XDT, 1>(a, grid, st);
+    case 3: return launch_multi_ub<3, XDT, 1>(a, grid, st);
+    default: return launch_multi_ub<4, XDT, 1>(a, grid, st);
   }
 }
 
 hipError_t launch_gemv_multi(const Layer* const* Ls, int n, int k, const void* x, aqmb_dtype x_dtype, int batch,
                              void* const* ys, aqmb_dtype y_dtype, hipStream_t st) {
-  // One launch when every layer takes the direct-gather path in a single batch tile (8-bit codes,
-  // k <= 4, batch <= 4) and, for rows of more than 512 groups, k = 1 (two layers' code words for
-  // several blocks do not fit in registers beyond one plane); otherwise the layers are launched
-  // one after another.
+  // One launch when every layer takes the direct-gather path (8-bit codes, k <= 4) at batch 1 and, for
+  // rows of more than 512 groups, k = 1 (two blocks' code words do not fit in registers beyond one
+  // plane); otherwise the layers are launched one after another.
   const Layer& L0 = *Ls[0];
-  bool one = batch <= 4 && cw_fits(k, batch, L0.S, x_dtype == AQMB_BF16) && (cw_blocks(L0.S) == 1 || k == 1);
+  bool one = batch == 1 && cw_fits(k, 1, L0.S, x_dtype == AQMB_BF16) && (cw_blocks(L0.S) == 1 || k == 1);
   for (int i = 0; i < n && one; ++i) one = Ls[i]->d.code_bits == 8;
   if (!one) {
     for (int i = 0; i < n; ++i) {
@@ -1150,7 +1085,6 @@ hipError_t launch_gemv_multi(const Layer* const* Ls, int n, int k, const void* x
     return hipSuccess;
   }
   GemvMultiArgs a{};
-  int grid = 0;
   for (int i = 0; i < n; ++i) {
     const Layer& L = *Ls[i];
     a.L[i].codes = L.codes;
@@ -1160,15 +1094,16 @@ hipError_t launch_gemv_multi(const Layer* const* Ls, int n, int k, const void* x
     a.L[i].plane_bytes = L.plane_bytes;
     a.L[i].d_out = L.d.d_out;
     a.L[i].row_blocks = (L.d.d_out + cw::kRows - 1) / cw::kRows;
-    grid = a.L[i].row_blocks > grid ? a.L[i].row_blocks : grid;
+    a.L[i].first = a.total;
+    a.total += a.L[i].row_blocks;
   }
   a.x = x;
   a.zero_page = L0.zero_page();
   a.n_layers = n;
   a.d_in = L0.d.d_in;
   a.S = L0.S;
-  a.batch = batch;
   a.y_dtype = (int)y_dtype;
+  const int ncu = L0.n_cu > 0 ? L0.n_cu : 256, grid = a.total < ncu ? a.total : ncu;
   return x_dtype == AQMB_F16 ? launch_multi_x<AQMB_F16>(a, k, grid, st) : launch_multi_x<AQMB_BF16>(a, k, grid, st);
 }
 

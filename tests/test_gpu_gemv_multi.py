@@ -120,3 +120,12 @@ def test_matrix_core_grid_sixteen_layers():
     assert A.MAX_MULTI == 16
     specs = [LayerSpec(f"s{i}", 1 + 32 * i, 264, M=3, seed=90 + i) for i in range(16)]
     _check(specs, (2, 9), (1, 3), ydts=("f32",))
+
+
+@pytest.mark.parametrize("heights", [(11008, 11008), (4096, 1024, 1024), (5000, 17, 4112), (16,) * 16])
+def test_row_blocks_shared_out_over_layers(heights):
+    """Batch 1: the layers' row blocks in one sequence, cut into even ranges for the compute units:
+    ranges that cross a layer boundary, ragged last blocks, fewer blocks than compute units."""
+    _check([LayerSpec(f"r{i}", h, 264, seed=400 + i) for i, h in enumerate(heights)], (1,), (1, 2, 3, 4), xdt="bf16",
+           ydts=("bf16",))
+    _check([LayerSpec(f"f{i}", h, 136, M=3, seed=420 + i) for i, h in enumerate(heights)], (1,), (1, 3))
