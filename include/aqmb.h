@@ -172,13 +172,13 @@ aqmb_status aqmb_gemv_select(aqmb_layer_t layer, int k, const void* x, aqmb_dtyp
  * same rounding), in one launch when either
  *   - every layer has 8-bit codes, k <= 4, aqmb_gemv would use the direct-gather kernel (batch 1;
  *     on rows of more than 512 groups only bf16 x at k < 3) and, for rows of more than 512
- *     groups, k = 1 (one workgroup per row block walks through the layers, loading the next
- *     layer's codes while it works on the current one), or
+ *     groups, k = 1, or
  *   - n_layers >= 2, every layer would take the matrix-core kernel (batch >= 2, and batch 1 on
- *     rows of more than 512 groups: see aqmb_gemv's kernel choice in the library source), all
- *     have the same code width and none has more 16-row blocks than the device has compute units
- *     (one grid over all the layers' row blocks);
- * otherwise the layers are launched one after another.
+ *     rows of more than 512 groups: see aqmb_gemv's kernel choice in the library source) and all
+ *     have the same code width (layers on both sides of the device's compute-unit count, in 16-row
+ *     blocks, only where aqmb_gemv treats bf16 x alike in both);
+ * otherwise the layers are launched one after another. In one launch the row blocks of all layers
+ * are shared out evenly over the compute units.
  *   layers  n_layers live handles, all with the same d_in and on the same device
  *   x       [batch][d_in], dtype x_dtype in {F16, BF16}
  *   ys      n_layers device pointers, ys[l] is [batch][d_out of layer l], dtype y_dtype
@@ -207,8 +207,10 @@ aqmb_status aqmb_gemm(aqmb_layer_t layer, int k, const void* X, int n_tokens, vo
 
 /*
  * The prefill GEMM's tilings (the same arithmetic and rounding; they differ in speed only).
- *   AQMB_GEMM_AUTO     the library's choice (what aqmb_gemm runs): 16-row tiles up to 144 tokens,
- *                      else the large tile that needs the fewest rounds of workgroups
+ *   AQMB_GEMM_AUTO     the library's choice (what aqmb_gemm runs): from 17 tokens and up to k = 4 a
+ *                      kernel that splits the inputs over a workgroup's waves, where it is estimated
+ *                      faster; else 16-row tiles up to 144 tokens, else the large tile that needs
+ *                      the fewest rounds of workgroups
  *   AQMB_GEMM_ROWS16   16 weight rows per workgroup, all tokens in tiles of 16 (made for few tokens)
  *   AQMB_GEMM_256x128, AQMB_GEMM_128x128, AQMB_GEMM_128x64
  *                      tokens x weight rows per workgroup of the large-tile kernel

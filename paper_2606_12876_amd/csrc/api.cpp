@@ -388,18 +388,17 @@ aqmb_status aqmb_gemv_multi(const aqmb_layer_t* layers, int n_layers, int k, con
   if (s != AQMB_OK) return s;
   // The one-launch kernels share the single-layer kernels' arithmetic, so the results are always
   // those of aqmb_gemv: the direct-gather multi-layer kernel when every layer would take the
-  // direct-gather kernel; the matrix-core grid over all layers' row blocks when every layer would
-  // take the one-block matrix-core kernel (same code width, at most one block per compute unit:
-  // taller layers run their persistent kernel, one launch each); otherwise one launch per layer.
+  // direct-gather kernel; the matrix-core kernels over all layers' row blocks when every layer would
+  // take the matrix cores (same code width, and the same form for bf16 x); otherwise one launch per
+  // layer.
   bool per_layer = false, all_mma = true;
   for (int i = 0; i < n_layers; ++i) {
     const aqmb_gemv_kernel kern = gemv_auto(*Ls[i], k, batch, x_dtype);
     const bool mma = kern == AQMB_GEMV_MMA;
     per_layer = per_layer || Ls[i]->d.code_bits != 8 || kern != AQMB_GEMV_DIRECT;
-    all_mma = all_mma && mma && Ls[i]->d.code_bits == Ls[0]->d.code_bits &&
-              (Ls[i]->d.d_out + 15) / 16 <= Ls[i]->n_cu;
+    all_mma = all_mma && mma && Ls[i]->d.code_bits == Ls[0]->d.code_bits;
   }
-  if (all_mma && n_layers >= 2) {
+  if (all_mma && n_layers >= 2 && gemv_mma_multi_fits(Ls, n_layers, k, batch, x_dtype)) {
     hipError_t e = launch_gemv_mma_multi(Ls, n_layers, k, x, x_dtype, batch, ys, y_dtype, (hipStream_t)stream);
     return e == hipSuccess ? AQMB_OK : hip_fail(e, "gemv_multi: launch");
   }

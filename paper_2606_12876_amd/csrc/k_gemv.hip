@@ -805,8 +805,10 @@ struct GemvMultiArgs {
 // of the current block (every wave has finished its gathers by then) and one more barrier publishes
 // them. Row sums alternate between two buffers, so that no barrier is needed between blocks of one
 // layer. UB = 512-group blocks per row (x in registers for every block at UB = 1).
-// Measured, batch 1, bf16 x, against a workgroup per row block walking through the layers, which
-// replicated the codebooks at every layer: see launch_gemv_multi.
+// Measured, batch 1, bf16 x, k = 4, against a workgroup per row block walking through the layers, which
+// replicated the codebooks at every layer: 2 x 11008 x 4096 24.7 -> 18.6 us (two single calls: 20.1),
+// 3 x 4096 x 4096 12.8 -> 11.9, 16 x 4096 x 4096 55.9 -> 45.9, 4096 + 2 x 1024 rows 12.1 -> 9.4;
+// 8 x 1024 x 1024 18.0 -> 6.6.
 template <int K, int XDT, int UB, bool PL>
 __global__ __launch_bounds__(cw::kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void gemv_cw_multi_kernel(GemvMultiArgs a) {

@@ -627,6 +627,7 @@ struct GemvMmaMultiArgs {
   GemvMmaArgs L[AQMB_MAX_MULTI];
   int first[AQMB_MAX_MULTI + 1];
   int n;
+  int low;                    // no layer has more row blocks than there are compute units
 };
 static_assert(sizeof(GemvMmaMultiArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 
@@ -718,19 +719,130 @@ void gemv_mma_persist_kernel(GemvMmaArgs a) {
   }
 }
 
+// Several layers whose row blocks outnumber the compute units, one launch: the row blocks of all
+// layers form one sequence, layer after layer, and a persistent workgroup per CU takes an even,
+// contiguous range of it, walked as in gemv_mma_persist_kernel. Most ranges stay within one layer, so a
+// workgroup pays its start (x, the codebook replicas) once and not once per layer; where a range
+// crosses to another layer, that layer's replicas are written after the reduction barrier of the last
+// block (every wave has finished its gathers by then) and one more barrier publishes them. P: the form
+// that the layers' own launches take for bf16 x (mg_split_p), so that the results are theirs.
+// Measured against a one-block workgroup per row block (taller layers: a persistent launch each),
+// bf16 x, k = 3: 3 x 4096 x 4096 at batch 11 22.1 -> 13.9 us, batch 2 14.9 -> 11.8; 16 layers at batch
+// 11 117 -> 45 us; 2 x 11008 x 4096 at batch 11 23.2 -> 19.9. A single layer keeps
+// gemv_mma_persist_kernel: walking one layer here is 5-10 % slower.
+template <int K, int XDT, int CB, int NX, bool P>
+__global__ __launch_bounds__(mg::kThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void gemv_mma_walk_kernel(GemvMmaMultiArgs m) {
+  using namespace mg;
+  constexpr bool kSpl = mg_split_p<K, XDT, NX, P>();
+  constexpr int kBooks = kSpl ? 2 : 1;                       // fp16 codewords, or bf16 high and low parts
+  extern __shared__ uint4 smem_mg[];
+  uint4* cb_rep = smem_mg;                                   // paired regions, or [kBooks][K][NCW][nrep] codewords
+  f32x4_t* red = (f32x4_t*)(smem_mg + (mg_paired<K, CB, kSpl>() ? mg_regions<K, kSpl>() * (kMgRegion / 16)
+                                                                 : kBooks * K * (1 << CB) * m.L[0].nrep));   // [2][kWaves][64] partial tiles
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15;
+  const int n_runs = (m.L[0].G + 15) / 16;
+  const int per = (n_runs + kWaves - 1) / kWaves;            // items per block, the same for every wave
+  const int total = m.first[m.n];
+  const int lo = (int)(((long long)blockIdx.x * total) / gridDim.x);
+  const int nb = (int)(((long long)(blockIdx.x + 1) * total) / gridDim.x) - lo;   // this workgroup's blocks
+  const int n_items = per * nb;
+  const uint32_t rep_off = (uint32_t)(lane & (m.L[0].nrep - 1)) * 16;
+  // The layer in hand on each side of the pipeline, held in registers: the loads run up to two items
+  // ahead of the products. (Indexing the kernel arguments at every item would put scalar loads, and
+  // with them a wait for every LDS read, into each item.)
+  struct Pos { GemvMmaArgs L; int layer, first, next; };     // rows of blocks first .. next - 1
+  auto move_to = [&](Pos& p, int blk) {                      // blk >= p.first
+    if (blk >= p.next) {
+      do { ++p.layer; } while (blk >= m.first[p.layer + 1]);
+      p.first = m.first[p.layer];
+      p.next = m.first[p.layer + 1];
+      p.L = m.L[p.layer];
+    }
+  };
+  Pos pc{m.L[0], 0, 0, m.first[1]};
+  move_to(pc, lo);
+  Pos pl = pc;
+  int li = 0, lblk = lo, lrun = wave;                        // the next item to load: its number, block, run
+  auto load_item = [&](MgRun<K, CB, NX>& R) {                // (items past the end: the last item again, never used)
+    const int row = (lblk - pl.first) * kRows + col;
+    mg_load_run<K, CB, NX, mg_swap_pairs<K, CB, kSpl>()>(pl.L, lrun, row < pl.L.d_out ? row : pl.L.d_out - 1,
+                                                        lrun < n_runs, R, li < 2 || per > 2);
+    if (++li < n_items) {
+      lrun += kWaves;
+      if (lrun >= wave + per * kWaves) { lrun = wave; move_to(pl, ++lblk); }
+    }
+  };
+  auto scale_of = [&](const Pos& p, int blk) -> uint16_t {   // of the row this thread stores, in the block's group
+    const int row = (blk - p.first) * kRows + mg_out_row(tid & 255);
+    return mg_in_group((blk - lo) & 3) ? p.L.scales[row < p.L.d_out ? row : p.L.d_out - 1] : 0;
+  };
+  uint16_t sbits;
+  f32x4_t acc[4];
+  int blk = lo, left = per;                                  // the block in hand, its items to come
+  auto end_block = [&]() {
+    const bool more = blk + 1 < lo + nb, change = more && blk + 1 >= pc.next;
+    const int row0 = (blk - pc.first) * kRows, grp = (blk - lo) & 3;
+    uint4 w0 = make_uint4(0, 0, 0, 0);
+    if (!change) {
+      mg_reduce_store(pc.L, red + (grp & 1) * (kWaves * 64), acc, row0, sbits, grp);
+    } else {
+      const GemvMmaArgs done = pc.L;
+      move_to(pc, blk + 1);
+      w0 = mg_first_word<K, CB, kSpl>(pc.L);
+      mg_reduce_store(done, red + (grp & 1) * (kWaves * 64), acc, row0, sbits, grp);
+    }
+    ++blk;
+    left = per;
+    if (more) sbits = scale_of(pc, blk);
+    if (change) {
+      mg_replicate<K, CB, kSpl>(pc.L, cb_rep, w0);
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+
+  MgRun<K, CB, NX> ra, rb;
+  const uint4 w0 = mg_first_word<K, CB, kSpl>(pc.L);
+  sbits = scale_of(pc, lo);
+  load_item(ra);
+  mg_replicate<K, CB, kSpl>(pc.L, cb_rep, w0);
+  load_item(rb);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < n_items; i += 2) {
+    mg_compute<K, XDT, CB, NX, P>(pc.L, cb_rep, rep_off, ra, acc, i < 2 || per > 2);   // x loaded with the item
+    load_item(ra);
+    if (--left == 0) end_block();
+    if (i + 1 >= n_items) break;
+    mg_compute<K, XDT, CB, NX, P>(pc.L, cb_rep, rep_off, rb, acc, i < 2 || per > 2);
+    load_item(rb);
+    if (--left == 0) end_block();
+  }
+}
+
 // 16-codeword codebooks (4-bit codes) fill the LDS banks once: one copy reads without conflicts.
 // (mm: several layers in one launch; a is then mm->L[0].)
 template <int K, int XDT, int CB, int NX>
 static hipError_t launch_mma_knx(GemvMmaArgs a, GemvMmaMultiArgs* mm, hipStream_t st) {
   const int n_rb = (a.d_out + mg::kRows - 1) / mg::kRows;
-  const bool persist = !mm && n_rb > a.n_cu && a.n_cu > 0;   // one workgroup per CU walks the blocks
-  const bool split = persist ? mg_split_p<K, XDT, NX, true>() : mg_split<K, XDT, NX>();
-  // partial tiles: one buffer, two in the persistent kernel
+  const int blocks = mm ? mm->first[mm->n] : n_rb;
+  // One workgroup per CU walks the blocks, but not over layers that each fit the compute units with
+  // rows of more than 32 runs: x is then reloaded at every block, and one-block workgroups hide that
+  // better (two 4096 x 11008 layers, batch 2..11: walking 2-11 % slower).
+  const bool persist = blocks > a.n_cu && a.n_cu > 0 && !(mm && mm->low && (a.G + 15) / 16 > 2 * mg::kWaves);
+  const bool pform = n_rb > a.n_cu && a.n_cu > 0;            // the form of the layers' own launches (the same for all)
+  const bool split = pform ? mg_split_p<K, XDT, NX, true>() : mg_split<K, XDT, NX>();
+  // partial tiles: one buffer, two in the persistent kernels
   const size_t red = (size_t)(persist ? 2 : 1) * mg::kWaves * 64 * 16, book = (size_t)(split ? 2 : 1) * K * (1 << CB) * 16;
   const size_t budget = 160 * 1024 - 1024 - red;
-  const bool paired = persist ? mg_paired<K, CB, mg_split_p<K, XDT, NX, true>()>()
-                              : mg_paired<K, CB, mg_split<K, XDT, NX>()>();
-  const int regions = persist ? mg_regions<K, mg_split_p<K, XDT, NX, true>()>() : mg_regions<K, mg_split<K, XDT, NX>()>();
+  const bool paired = pform ? mg_paired<K, CB, mg_split_p<K, XDT, NX, true>()>()
+                            : mg_paired<K, CB, mg_split<K, XDT, NX>()>();
+  const int regions = pform ? mg_regions<K, mg_split_p<K, XDT, NX, true>()>() : mg_regions<K, mg_split<K, XDT, NX>()>();
   // otherwise (k > 4; k > 2 split): as many interleaved copies per codebook as fit
   a.nrep = CB == 4 ? 1 : paired ? 8 : book * 8 <= budget ? 8 : book * 4 <= budget ? 4 : 2;
   a.cb_shift = a.nrep == 8 ? 7 : a.nrep == 4 ? 6 : a.nrep == 2 ? 5 : 4;
@@ -740,12 +852,25 @@ static hipError_t launch_mma_knx(GemvMmaArgs a, GemvMmaMultiArgs* mm, hipStream_
       mm->L[l].nrep = a.nrep;
       mm->L[l].cb_shift = a.cb_shift;
     }
-    gemv_mma_multi_kernel<K, XDT, CB, NX><<<dim3(mm->first[mm->n]), mg::kThreads, lds, st>>>(*mm);
+    if (!persist) gemv_mma_multi_kernel<K, XDT, CB, NX><<<dim3(blocks), mg::kThreads, lds, st>>>(*mm);
+    else if (split == mg_split<K, XDT, NX>()) gemv_mma_walk_kernel<K, XDT, CB, NX, false><<<dim3(a.n_cu), mg::kThreads, lds, st>>>(*mm);
+    else if constexpr (mg_split_p<K, XDT, NX, true>() != mg_split<K, XDT, NX>())
+      gemv_mma_walk_kernel<K, XDT, CB, NX, true><<<dim3(a.n_cu), mg::kThreads, lds, st>>>(*mm);
     return hipGetLastError();
   }
   if (persist) gemv_mma_persist_kernel<K, XDT, CB, NX><<<dim3(a.n_cu), mg::kThreads, lds, st>>>(a);
   else gemv_mma_kernel<K, XDT, CB, NX><<<dim3(n_rb), mg::kThreads, lds, st>>>(a);
   return hipGetLastError();
+}
+
+// Whether one launch can serve the layers with the results of their own launches: bf16 x takes the
+// split or the converted form by k, batch and whether the layer outnumbers the compute units; layers
+// of both kinds only go together where the two forms agree.
+bool gemv_mma_multi_fits(const Layer* const* Ls, int n, int k, int batch, aqmb_dtype x_dtype) {
+  bool tall = false, low = false;
+  for (int l = 0; l < n; ++l) ((Ls[l]->d.d_out + mg::kRows - 1) / mg::kRows > Ls[l]->n_cu ? tall : low) = true;
+  if (!(tall && low) || x_dtype == AQMB_F16) return true;
+  return (k < 2) == (k < (batch <= 4 ? 2 : 3));              // mg_split_p with and without P
 }
 
 // x loads per run: batch rows in groups of 4 per 16-lane row (see MgRun).
@@ -804,10 +929,13 @@ hipError_t launch_gemv_mma_multi(const Layer* const* Ls, int n, int k, const voi
                                  void* const* ys, aqmb_dtype y_dtype, hipStream_t st) {
   GemvMmaMultiArgs m{};
   m.n = n;
+  m.low = 1;
   m.first[0] = 0;
   for (int l = 0; l < n; ++l) {
     m.L[l] = mma_args(*Ls[l], x, batch, ys[l], y_dtype);
-    m.first[l + 1] = m.first[l] + (Ls[l]->d.d_out + mg::kRows - 1) / mg::kRows;
+    const int n_rb = (Ls[l]->d.d_out + mg::kRows - 1) / mg::kRows;
+    m.first[l + 1] = m.first[l] + n_rb;
+    if (n_rb > Ls[l]->n_cu) m.low = 0;
   }
   const int cb = Ls[0]->d.code_bits;
   return x_dtype == AQMB_F16 ? launch_mma_x<AQMB_F16>(m.L[0], &m, k, cb, st)

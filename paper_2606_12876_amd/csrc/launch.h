@@ -30,6 +30,7 @@ hipError_t launch_gemv_mma(const Layer& L, int k, const void* x, aqmb_dtype x_dt
 // launch_gemv_mma's for each layer); n <= AQMB_MAX_MULTI.
 hipError_t launch_gemv_mma_multi(const Layer* const* Ls, int n, int k, const void* x, aqmb_dtype x_dtype, int batch,
                                  void* const* ys, aqmb_dtype y_dtype, hipStream_t st);
+bool gemv_mma_multi_fits(const Layer* const* Ls, int n, int k, int batch, aqmb_dtype x_dtype);
 // Decode GEMV of a layer with 4-bit codes (16-codeword codebooks).
 hipError_t launch_gemv_b4(const Layer& L, int k, const void* x, aqmb_dtype x_dtype, int batch, void* y,
                           aqmb_dtype y_dtype, hipStream_t st);

@@ -129,3 +129,14 @@ def test_row_blocks_shared_out_over_layers(heights):
     _check([LayerSpec(f"r{i}", h, 264, seed=400 + i) for i, h in enumerate(heights)], (1,), (1, 2, 3, 4), xdt="bf16",
            ydts=("bf16",))
     _check([LayerSpec(f"f{i}", h, 136, M=3, seed=420 + i) for i, h in enumerate(heights)], (1,), (1, 3))
+
+
+@pytest.mark.parametrize("heights,d_in", [((4112, 4096, 33), 264), ((5000, 4500), 264), ((2100, 2100, 2100), 2184),
+                                          ((4096, 4090), 4360), ((4100, 4100), 4360)])
+def test_matrix_core_walk_over_layers(heights, d_in):
+    """Batch above 1, more row blocks than compute units: ranges that cross layer boundaries, layers
+    on both sides of the compute-unit count (at k = 2 and batch 9 their bf16 forms differ), rows of
+    at most 16, 32 and more than 32 runs."""
+    specs = [LayerSpec(f"w{i}", h, d_in, seed=440 + i) for i, h in enumerate(heights)]
+    _check(specs, (3, 9), (1, 2, 4), xdt="bf16", ydts=("bf16",))
+    _check(specs, (5,), (1, 3), ydts=("f32",))
