@@ -125,3 +125,20 @@ def _misaligned(gl, X, n, Y, ws, nb):
                             ctypes.c_void_p(ws.data_ptr() + 16), nb, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     if st != A.Status.OK:
         raise A.AqmbError(st, "aqmb_gemm_ws", "")
+
+
+def test_quantlinear_takes_the_workspace_path():
+    """QuantLinear.forward passes a workspace where the two-pass path applies: the result is aqmb_gemm's,
+    also on inputs of leading dimensions, and without memory for the workspace."""
+    spec = LayerSpec("ql", 4096, 1024, M=3, seed=305)
+    L = make_layer(spec)
+    X = to_dev(make_activations(L, 2048, "bf16")).view(torch.bfloat16)
+    lin = A.QuantLinear(to_dev(L.codes), to_dev(L.codebooks).view(torch.float16), to_dev(L.scales).view(torch.float16))
+    assert lin._workspace(3, 2048, X.device) is not None and lin._workspace(2, 2048, X.device) is None
+    one = torch.empty((2048, 4096), dtype=torch.bfloat16, device="cuda")
+    A.gemm(lin.handle, 3, X, 2048, one, A.DType.BF16)
+    assert torch.equal(lin(X, 3), one)
+    assert torch.equal(lin(X.reshape(2, 1024, 1024), 3), one.reshape(2, 1024, 4096))
+    lin._workspace = lambda k, n, device: None
+    assert torch.equal(lin(X, 3), one)
+    lin.close()
