@@ -39,6 +39,12 @@ __device__ __forceinline__ void load_lds16(const void* gptr, uint32_t lds_base) 
                :: "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory", "m0");
 }
 
+// Direct global->LDS load of 16 bytes per lane from base + off (base uniform), as load_lds16.
+__device__ __forceinline__ void load_lds16_off(const void* base, uint32_t off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(off), "s"(base) : "memory", "m0");
+}
+
 // s_waitcnt vmcnt(N), the other counters left at their maxima (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -31,7 +31,6 @@
 // compiler cannot see that their destinations are disjoint and would otherwise serialise them.
 // Every such load instruction is issued unconditionally (out-of-range rows and groups read a
 // valid address and are masked later), so each wait counts a fixed number of loads.
-#include <cstdlib>
 
 #include "device.h"
 #include "launch.h"
@@ -93,7 +92,7 @@ __global__ __launch_bounds__(64 * (CW + 4)) void gemm_kernel(const unsigned char
                                                               const uint16_t* __restrict__ scales,
                                                               const uint16_t* __restrict__ X, void* __restrict__ Y,
                                                               int n_tokens, int d_out, int d_in, int G,
-                                                              size_t plane_bytes, int n_tb, int n_cb) {
+                                                              size_t plane_bytes, int n_tb, int n_cb, int stagger) {
   using namespace gemm;
   constexpr int kDepth = x_depth<K>();
   constexpr int NCW = 1 << CB;
@@ -117,7 +116,7 @@ __global__ __launch_bounds__(64 * (CW + 4)) void gemm_kernel(const unsigned char
   const int tb = blockIdx.x % n_tb, cb = blockIdx.x / n_tb;
   const int n0 = tb * BMT, i0 = cb * BNT;
   const int nsteps = (d_in + BK - 1) / BK;
-  const int s0 = (int)(((long long)cb * nsteps) / n_cb);
+  const int s0 = stagger ? (int)(((long long)cb * nsteps) / n_cb) : 0;
   auto step_of = [&](int seq) { int st = s0 + seq; return st >= nsteps ? st - nsteps : st; };
 
   for (int q = tid; q < K * NCW; q += kThreads) cbs[q] = ((const uint4*)codebooks)[q];
@@ -516,20 +515,153 @@ __global__ __launch_bounds__(gemm2::kThreads) void gemm_dense_kernel(const uint1
   }
 }
 
-template <int K, int CB, int BMT, int BNT, int CW>
-static void launch_kcm(const Layer& L, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, hipStream_t st) {
-  using namespace gemm;
-  constexpr int kDepth = x_depth<K>();
-  const int n_tb = (n_tokens + BMT - 1) / BMT, n_cb = (L.d.d_out + BNT - 1) / BNT;
-  const size_t lds = ((size_t)kDepth * x_stage<BMT>() + 2 * slab_elems<BNT>()) * 2 + (size_t)K * (1 << CB) * 16 +
-                     (size_t)kCodeDepth * 4 * K * 64 * 4;
-  const dim3 grid(n_tb * n_cb);
-  if (y_dtype == AQMB_BF16)
-    gemm_kernel<K, AQMB_BF16, CB, BMT, BNT, CW><<<grid, 64 * (CW + 4), lds, st>>>(
-        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_cb);
-  else
-    gemm_kernel<K, AQMB_F32, CB, BMT, BNT, CW><<<grid, 64 * (CW + 4), lds, st>>>(
-        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_cb);
+// Pass 2 for problems with many tiles: 256 tokens x 256 weight rows per workgroup, 8 waves of 128 x 64
+// (4 x 2 MFMA blocks). Against the 256 x 128 tiles a step's LDS reads halve per product (each wave
+// reads 6 fragments for 8 MFMAs instead of 4 for 4), so the step is bound by the MFMAs; a stage (64
+// inputs, 64 KiB) is twice as long, so two stages suffice: the next one is loaded, by direct
+// global->LDS loads, while the current one is used, with one barrier per step. Both 128-row halves start
+// their K walk where gemm_kernel's column blocks do: same products in the same order.
+namespace gemm3 {
+constexpr int kWaves = 8, kThreads = 64 * kWaves, BM = 256, BN = 256, BK = 64;
+constexpr int kXStage = BM * BK, kStage = kXStage + BN * BK;   // bf16 values
+}  // namespace gemm3
+
+template <int YDT>
+__global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const uint16_t* __restrict__ Wt,
+                                                                       const uint16_t* __restrict__ scales,
+                                                                       const uint16_t* __restrict__ X, void* __restrict__ Y,
+                                                                       int n_tokens, int d_out, int d_in, int nsteps,
+                                                                       int n_tb, int n_cb, int n_c32) {
+  using namespace gemm3;
+  constexpr int MA = 4, NBB = 2;                   // 32 x 32 blocks per wave: 4 token x 2 weight row
+  extern __shared__ uint4 smem3[];
+  uint16_t* S = (uint16_t*)smem3;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, r32 = lane & 31;
+  // Workgroup w runs on XCD w mod 8: each XCD takes a contiguous range of the tiles, in groups of four
+  // token tiles walked column block by column block, so that the 32 workgroups of an XCD share the
+  // X rows of four token tiles and the weights of eight column blocks.
+  const int T = n_tb * n_cb, xcd = blockIdx.x & 7, jx = blockIdx.x >> 3;
+  const int per = T >> 3, rem = T & 7;             // XCD x: per (+ 1 for x < rem) tiles
+  const int t = xcd * per + (xcd < rem ? xcd : rem) + jx;
+  const int grp = t / (4 * n_cb), gt = t - grp * 4 * n_cb;
+  const int gw = n_tb - 4 * grp < 4 ? n_tb - 4 * grp : 4;
+  const int cb = gt / gw, tb = 4 * grp + gt % gw;
+  const int n0 = tb * BM, i0 = cb * BN;
+
+  // This lane's four X pieces of a stage as offsets from the tile's first token (rows past the last
+  // token read it again, never stored), and the wave's four weight chunks.
+  const int pos = lane & 7, rsub = lane >> 3;
+  const char* Xt = (const char*)(X + (size_t)n0 * d_in);
+  const uint32_t row_b = (uint32_t)d_in * 2, last = (uint32_t)(n_tokens - 1 - n0);
+  uint32_t xoff[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t r = wave * 32 + q * 8 + rsub;
+    xoff[q] = (r < last ? r : last) * row_b + (pos ^ ((r >> 1) & 7)) * 16;
+  }
+  int c32 = i0 / 32 + wave;                        // the wave loads the four K-blocks of one 32-row block
+  if (c32 >= n_c32) c32 = n_c32 - 1;               // rows past d_out: any valid tile, never stored
+  const char* Wc = (const char*)(Wt + (size_t)c32 * nsteps * 4 * gemm::kChunk);
+  const uint32_t woff = lane * 16;
+  auto load_stage = [&](int st) {
+    uint16_t* stage = S + (st & 1) * kStage;
+    const char* wsrc = Wc + (size_t)st * 4 * gemm::kChunk * 2;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      load_lds16_off(wsrc + q * gemm::kChunk * 2, woff, lds_addr(stage + kXStage + (wave * 4 + q) * gemm::kChunk));
+    const char* xsrc = Xt + (size_t)st * BK * 2;
+    if (st * BK + BK <= d_in) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) load_lds16_off(xsrc, xoff[q], lds_addr(stage + (wave * 32 + q * 8) * BK));
+    } else {                                       // the ragged last step: zero past d_in
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = wave * 32 + q * 8 + rsub, kc = pos ^ ((r >> 1) & 7);
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (st * BK + kc * 8 < d_in) v = *(const uint4*)(xsrc + xoff[q]);
+        *(uint4*)(stage + (wave * 32 + q * 8) * BK + lane * 8) = v;
+      }
+    }
+  };
+  const int wm = wave >> 2, wn = wave & 3;         // tokens 128 wm .., weight rows 64 wn ..
+  f32x16_t acc[MA][NBB];
+#pragma unroll
+  for (int a = 0; a < MA; ++a)
+#pragma unroll
+    for (int b = 0; b < NBB; ++b)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+  struct Frags { bf16x8_t a[MA], b[NBB]; };
+  auto read_frags = [&](const uint16_t* xst, int i, Frags& f) {
+    const uint16_t* bsl = xst + kXStage;
+#pragma unroll
+    for (int b = 0; b < NBB; ++b) f.b[b] = *(const bf16x8_t*)(bsl + ((wn * NBB + b) * 4 + i) * gemm::kChunk + lane * 8);
+    const int kc = 2 * i + half;
+#pragma unroll
+    for (int a = 0; a < MA; ++a) {
+      const int r = wm * 128 + a * 32 + r32;
+      f.a[a] = *(const bf16x8_t*)(xst + r * BK + ((kc ^ ((r >> 1) & 7)) * 8));
+    }
+  };
+  auto mfmas = [&](const Frags& f) {
+#pragma unroll
+    for (int a = 0; a < MA; ++a)
+#pragma unroll
+      for (int b = 0; b < NBB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a], f.b[b], acc[a][b], 0, 0, 0);
+  };
+  auto interleave = [&]() {                        // the next fragments' reads between the products
+#pragma unroll
+    for (int q = 0; q < MA + NBB; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, MA * NBB - MA - NBB, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load_stage(0);
+  wait_vmcnt<0>();
+  __syncthreads();
+  if (nsteps > 1) load_stage(1);
+  Frags f0, f1;
+  read_frags(S, 0, f0);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int st = 0; st < nsteps; ++st) {
+    const uint16_t* xst = S + (st & 1) * kStage;
+    read_frags(xst, 1, f1);
+    mfmas(f0);
+    interleave();
+    read_frags(xst, 2, f0);
+    mfmas(f1);
+    interleave();
+    read_frags(xst, 3, f1);
+    mfmas(f0);
+    interleave();
+    // Every fragment of this stage is in registers (of this wave, then of all): its buffer is free
+    // for the stage after next, and the next stage's first fragments are read under the last products.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (st + 2 < nsteps) load_stage(st + 2);
+    if (st + 1 < nsteps) read_frags(S + ((st + 1) & 1) * kStage, 0, f0);
+    mfmas(f1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int b = 0; b < NBB; ++b) {
+    const int col = i0 + wn * 64 + b * 32 + r32;
+    if (col >= d_out) continue;
+    const float scale = f16_to_f32(scales[col]);
+#pragma unroll
+    for (int a = 0; a < MA; ++a) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = n0 + wm * 128 + a * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+        if (row < n_tokens) OutT<YDT>::store(Y, (size_t)row * d_out + col, acc[a][b][e] * scale);
+      }
+    }
+  }
 }
 
 // Tile shape: 0 = 256 tokens x 128 rows, 1 = 128 x 128, 2 = 128 x 64. Unless the caller names one,
@@ -551,6 +683,45 @@ static int gemm_tile(const Layer& L, int n_tokens, int forced) {
   return best;
 }
 
+// Rounds of workgroups, one per compute unit; a last round that is not full counts at least 0.7.
+static double gemm_rounds(const Layer& L, int n_tokens, int bm, int bn) {
+  const long long ncu = L.n_cu > 0 ? L.n_cu : 256;
+  const long long wg = (long long)((n_tokens + bm - 1) / bm) * ((L.d.d_out + bn - 1) / bn);
+  if (wg <= ncu) return 1.0;
+  const double part = (double)(wg % ncu) / ncu;
+  return (double)(wg / ncu) + (part > 0 && part < 0.7 ? 0.7 : part);
+}
+
+// Whether the dense pass takes 256 x 256 tiles: where the library's choice is the 256 x 128 tiling with
+// every compute unit busy and the larger tiles' rounds cost less (a round measured 116 us on a 4096-input
+// layer, 68.5 us for 256 x 128 tiles; 2048 tokens x 4096 rows: half the compute units would idle). At
+// these sizes every GEMM kernel starts its K walk at the first step: the staggered starts that keep
+// the column blocks of one round off the same X rows cost more than they save over several rounds
+// (8192 x 4096 x 4096, one pass, k = 1: 285 -> 269 us; 4096 tokens x 4096 x 11008: 381 -> 344 us).
+static bool gemm_dense256(const Layer& L, int n_tokens) {
+  if (gemm_tile(L, n_tokens, -1) != 0 || L.d.d_in > (1 << 20)) return false;
+  const long long wg = (long long)((n_tokens + gemm2::BM - 1) / gemm2::BM) * ((L.d.d_out + gemm2::BN - 1) / gemm2::BN);
+  if (wg < (L.n_cu > 0 ? L.n_cu : 256)) return false;
+  return 116.0 * gemm_rounds(L, n_tokens, gemm3::BM, gemm3::BN) < 68.5 * gemm_rounds(L, n_tokens, gemm2::BM, gemm2::BN);
+}
+
+template <int K, int CB, int BMT, int BNT, int CW>
+static void launch_kcm(const Layer& L, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, hipStream_t st) {
+  using namespace gemm;
+  const int stagger = !gemm_dense256(L, n_tokens);
+  constexpr int kDepth = x_depth<K>();
+  const int n_tb = (n_tokens + BMT - 1) / BMT, n_cb = (L.d.d_out + BNT - 1) / BNT;
+  const size_t lds = ((size_t)kDepth * x_stage<BMT>() + 2 * slab_elems<BNT>()) * 2 + (size_t)K * (1 << CB) * 16 +
+                     (size_t)kCodeDepth * 4 * K * 64 * 4;
+  const dim3 grid(n_tb * n_cb);
+  if (y_dtype == AQMB_BF16)
+    gemm_kernel<K, AQMB_BF16, CB, BMT, BNT, CW><<<grid, 64 * (CW + 4), lds, st>>>(
+        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_cb, stagger);
+  else
+    gemm_kernel<K, AQMB_F32, CB, BMT, BNT, CW><<<grid, 64 * (CW + 4), lds, st>>>(
+        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_cb, stagger);
+}
+
 // One round of 256 workgroups measured on a 4096-input layer (k = 1..4, us), the part above 5 us in
 // proportion to d_in; a last round that is not full counts 0.7 (11008 x 4096, 900 tokens, 1.34 rounds
 // of 256 x 128: 165 us at k = 4, 128 us at k = 1).
@@ -558,10 +729,7 @@ double gemm_large_us(const Layer& L, int k, int n_tokens) {
   static const double us[3][4] = {{72.0, 77.5, 86.6, 96.8}, {52.0, 60.0, 68.0, 77.0}, {36.0, 41.0, 47.0, 53.0}};
   const int bm[3] = {256, 128, 128}, bn[3] = {128, 128, 64};
   const int c = gemm_tile(L, n_tokens, -1);
-  const long long ncu = L.n_cu > 0 ? L.n_cu : 256;
-  const long long wg = (long long)((n_tokens + bm[c] - 1) / bm[c]) * ((L.d.d_out + bn[c] - 1) / bn[c]);
-  const double rounds = wg <= ncu ? 1.0 : (double)(wg / ncu) + (wg % ncu ? 0.7 : 0.0);
-  return rounds * (5.0 + (us[c][k - 1] - 5.0) * L.d.d_in / 4096.0);
+  return gemm_rounds(L, n_tokens, bm[c], bn[c]) * (5.0 + (us[c][k - 1] - 5.0) * L.d.d_in / 4096.0);
 }
 
 template <int K, int CB>
@@ -603,15 +771,23 @@ hipError_t launch_gemm(const Layer& L, int k, const void* X, int n_tokens, void*
 }
 
 
-// Workspace bytes of the two-pass GEMM (0: the path does not apply). It applies at k >= 3 with 4-
-// or 8-bit codes where the library's choice is the 256 x 128 tiling with at least one workgroup
-// per compute unit (the same per-output arithmetic as that tiling). At k <= 2 the one-pass kernel
-// with eight consumer waves is as fast (2048 x 4096 x 4096, k = 2: 77.5 us against 80.1).
+// Workspace bytes of the two-pass GEMM (0: the path does not apply). It applies with 4- or 8-bit codes
+// where the library's choice is the 256 x 128 tiling with at least one workgroup per compute unit (the
+// same per-output arithmetic as that tiling): at k >= 3 always, at k <= 2 where the dense pass takes
+// 256 x 256 tiles and both passes are estimated faster than the one-pass kernel with eight consumer
+// waves (8192 x 11008 x 4096: 739 us at k = 1 and 802 at k = 2 in one pass, 697 in two; 2048 x 4096 x
+// 4096, k = 2: 77.5 in one pass, 80.1 in two).
 size_t gemm_two_pass_bytes(const Layer& L, int k, int n_tokens) {
-  if (k < 3 || (L.d.code_bits != 8 && L.d.code_bits != 4)) return 0;
+  if (L.d.code_bits != 8 && L.d.code_bits != 4) return 0;
   if (gemm_tile(L, n_tokens, -1) != 0) return 0;
   const long long wg = (long long)((n_tokens + gemm2::BM - 1) / gemm2::BM) * ((L.d.d_out + gemm2::BN - 1) / gemm2::BN);
   if (wg < (L.n_cu > 0 ? L.n_cu : 256)) return 0;
+  if (k < 3) {
+    if (!gemm_dense256(L, n_tokens)) return 0;
+    const double len = L.d.d_in / 4096.0, one = (k == 1 ? 70.0 : 76.0) * len * gemm_rounds(L, n_tokens, gemm2::BM, gemm2::BN);
+    const double two = 2.0 + 9.0 * len * L.d.d_out / 4096.0 + 116.0 * len * gemm_rounds(L, n_tokens, gemm3::BM, gemm3::BN);
+    if (two > 0.97 * one) return 0;
+  }
   const size_t n_c32 = (L.d.d_out + 31) / 32, nsteps = (L.d.d_in + gemm2::BK - 1) / gemm2::BK;
   return n_c32 * nsteps * 4 * gemm::kChunk * 2;
 }
@@ -638,6 +814,7 @@ hipError_t launch_gemm_two_pass(const Layer& L, int k, const void* X, int n_toke
   const int n_c32 = (L.d.d_out + 31) / 32, nsteps = (L.d.d_in + BK - 1) / BK;
   uint16_t* Wt = (uint16_t*)workspace;
   switch (k) {
+    case 1: launch_wtile_k<1>(L, Wt, n_c32, nsteps, st); break;
     case 2: launch_wtile_k<2>(L, Wt, n_c32, nsteps, st); break;
     case 3: launch_wtile_k<3>(L, Wt, n_c32, nsteps, st); break;
     case 4: launch_wtile_k<4>(L, Wt, n_c32, nsteps, st); break;
@@ -645,6 +822,17 @@ hipError_t launch_gemm_two_pass(const Layer& L, int k, const void* X, int n_toke
     case 6: launch_wtile_k<6>(L, Wt, n_c32, nsteps, st); break;
     case 7: launch_wtile_k<7>(L, Wt, n_c32, nsteps, st); break;
     default: launch_wtile_k<8>(L, Wt, n_c32, nsteps, st); break;
+  }
+  if (gemm_dense256(L, n_tokens)) {
+    const int n_tb = (n_tokens + gemm3::BM - 1) / gemm3::BM, n_cb = (L.d.d_out + gemm3::BN - 1) / gemm3::BN;
+    const size_t lds = (size_t)2 * gemm3::kStage * 2;
+    if (y_dtype == AQMB_BF16)
+      gemm_dense256_kernel<AQMB_BF16><<<n_tb * n_cb, gemm3::kThreads, lds, st>>>(Wt, L.scales, (const uint16_t*)X, Y, n_tokens,
+                                                                               L.d.d_out, L.d.d_in, nsteps, n_tb, n_cb, n_c32);
+    else
+      gemm_dense256_kernel<AQMB_F32><<<n_tb * n_cb, gemm3::kThreads, lds, st>>>(Wt, L.scales, (const uint16_t*)X, Y, n_tokens,
+                                                                              L.d.d_out, L.d.d_in, nsteps, n_tb, n_cb, n_c32);
+    return hipGetLastError();
   }
   const int n_tb = (n_tokens + BM - 1) / BM, n_cb = (L.d.d_out + BN - 1) / BN;
   // XCD blocks: token tiles in ga groups, column blocks in gb groups, ga * gb = 8

@@ -83,11 +83,6 @@ template <int K> __device__ __forceinline__ b16x8_t fold(const uint4 (&c)[K]) {
   return __builtin_bit_cast(b16x8_t, make_uint4(pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]),
                                                 pack_bf16x2(w[4], w[5]), pack_bf16x2(w[6], w[7])));
 }
-// Direct global->LDS load of 16 bytes per lane from base + off (base uniform), as load_lds16.
-__device__ __forceinline__ void load_lds16_off(const void* base, uint32_t off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(off), "s"(base) : "memory", "m0");
-}
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 template <int K, int CB, int RB, int NB>
