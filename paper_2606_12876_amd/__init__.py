@@ -445,7 +445,7 @@ class QuantLinear:
             if st:
                 _check(st, "aqmb_gemv")
         else:
-            ws = self._workspace(k, n, x.device) if k > 2 else None
+            ws = self._workspace(k, n, x.device)
             st = lib.aqmb_gemm_ws(self.handle, k, x2.data_ptr(), n, y.data_ptr(), _torch_dt(y),
                                   None if ws is None else ws.data_ptr(), 0 if ws is None else ws.numel(), _stream(None))
             if st:

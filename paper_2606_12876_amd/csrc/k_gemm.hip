@@ -38,7 +38,7 @@
 namespace aqmb {
 
 namespace gemm {
-constexpr int BM = 256, BN = 128, BK = 64;
+constexpr int BK = 64;
 template <int K> constexpr int x_depth() { return K <= 4 ? 3 : 2; }   // X stages (LDS budget)
 template <int BMT> constexpr int x_stage() { return BMT * BK; }   // bf16 elements: BMT rows x 128 bytes
 constexpr int kChunk = 512;                          // one weight fragment: 64 lanes x 8 bf16
@@ -317,11 +317,6 @@ __global__ __launch_bounds__(64 * (CW + 4)) void gemm_kernel(const unsigned char
 // past d_in), which is also the order of a weight slab in gemm_kernel's LDS.
 namespace gemm2 {
 constexpr int kTileWaves = 4, kRep = 2;            // tiling pass: 4 waves, two codebook copies
-constexpr int kWaves = 8, kThreads = 64 * kWaves;  // dense pass: 8 waves (two per SIMD)
-constexpr int BM = 256, BN = 128, BK = 64, kDepth = 3;
-constexpr int kXStage = BM * BK;                   // bf16 values: 256 rows x 128 bytes
-constexpr int kSlab = (BN / 32) * 4 * gemm::kChunk;
-constexpr int kStage = kXStage + kSlab;
 }  // namespace gemm2
 
 // Pass 1. A wave takes 32 weight rows and two K-steps (lane l: row l % 32, step l / 32), a
@@ -382,158 +377,33 @@ __global__ __launch_bounds__(64 * gemm2::kTileWaves) void gemm_wtile_kernel(cons
   }
 }
 
-// Pass 2: 256 x 128 output tiles, 8 waves (two per SIMD) of 64 tokens x 64 weight rows (2 x 2 MFMA
-// blocks of 32 x 32), d_in in steps of 64 through a ring of three LDS stages, each holding the
-// step's X rows (the swizzled layout of gemm_kernel) and its weight tile, both filled by direct
-// global->LDS loads two steps ahead; one barrier per step. Column blocks start their K walk at the
-// steps gemm_kernel uses. Workgroups are placed on XCDs (workgroup w runs on XCD w mod 8) in a
-// grid of ga x gb blocks of token tiles x column blocks, so that the workgroups sharing weight
-// tiles and X rows share an L2 (ga = 0: the plain order).
-template <int YDT>
-__global__ __launch_bounds__(gemm2::kThreads) void gemm_dense_kernel(const uint16_t* __restrict__ Wt,
-                                                                    const uint16_t* __restrict__ scales,
-                                                                    const uint16_t* __restrict__ X, void* __restrict__ Y,
-                                                                    int n_tokens, int d_out, int d_in, int nsteps,
-                                                                    int n_tb, int n_cb, int n_c32, int ga, int gb) {
-  using namespace gemm2;
-  constexpr int MA = 2, NBB = 2;                   // 32 x 32 blocks per wave: 2 token x 2 weight row
-  constexpr int kXLoads = BM / (8 * kWaves), kWLoads = BN / (8 * kWaves), kLoads = kXLoads + kWLoads;
-  constexpr int kRowsW = BM / kWaves;              // X rows loaded by each wave
-  extern __shared__ uint4 smem2[];
-  uint16_t* S = (uint16_t*)smem2;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int half = lane >> 5, r32 = lane & 31;
-  int tb = blockIdx.x % n_tb, cb = blockIdx.x / n_tb;
-  if (ga > 0) {
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, per_cb = n_cb / gb, per_tb = n_tb / ga;
-    cb = per_cb * (xcd % gb) + j % per_cb;
-    tb = per_tb * (xcd / gb) + j / per_cb;
-  }
-  const int n0 = tb * BM, i0 = cb * BN;
-  const int s0 = (int)(((long long)cb * nsteps) / n_cb);
-  auto step_of = [&](int seq) { int st = s0 + seq; return st >= nsteps ? st - nsteps : st; };
+// Pass 2: BM x BN output tiles (256 tokens x 256 weight rows, or x 128 where the larger tiles would
+// leave compute units idle), 8 waves of 128 x 64 (64 x 64), d_in in steps of 64 through a ring of two
+// (three) LDS stages of X rows (the swizzled layout of gemm_kernel) and weight chunks, both filled by
+// direct global->LDS loads. One barrier per step, placed before the last K-block's products: every
+// fragment of the stage is in registers by then, so its buffer takes the next loads at once, and the
+// next stage's first fragments are read under those products. The 256-row tiles read 6 fragments for 8
+// MFMAs (4 for 4 on the others, whose LDS reads take as long as their MFMAs), so they are bound by the
+// MFMAs. Column blocks start their K walk where gemm_kernel's do: same products in the same order.
+// Measured with 256 x 256 tiles against 256 x 128 (both passes): 8192 x 11008 x 4096 780 -> 669 us,
+// 4096 x 4096 x 4096 153 -> 123 us.
+template <int BN> struct Dense {
+  static constexpr int BM = 256, BK = 64, kWaves = 8, kThreads = 64 * kWaves;
+  static constexpr int kDepth = BN == 256 ? 2 : 3, kWN = BN / 64, kWM = kWaves / kWN;   // waves across rows, tokens
+  static constexpr int MA = BM / kWM / 32, NBB = 2;                                     // 32 x 32 blocks per wave
+  static constexpr int kXLoads = 4, kWLoads = BN / 64;                                  // direct loads per wave and stage
+  static constexpr int kXStage = BM * BK, kStage = kXStage + BN * BK;                   // bf16 values
+};
 
-  auto load_stage = [&](int seq) {
-    const int st = step_of(seq);
-    const int k0 = st * BK;
-    uint16_t* stage = S + (seq % kDepth) * kStage;
-#pragma unroll
-    for (int t = 0; t < kWLoads; ++t) {            // chunk c: column block c / 4, K-block c % 4
-      const int c = wave * kWLoads + t;
-      int c32 = i0 / 32 + (c >> 2);
-      if (c32 >= n_c32) c32 = n_c32 - 1;           // rows past d_out: any valid tile, never stored
-      load_lds16(Wt + (((size_t)c32 * nsteps + st) * 4 + (c & 3)) * gemm::kChunk + lane * 8,
-                 lds_addr(stage + kXStage + c * gemm::kChunk));
-    }
-    const int pos = lane & 7, rsub = lane >> 3;
-    if (k0 + BK <= d_in) {
-#pragma unroll
-      for (int t = 0; t < kXLoads; ++t) {
-        const int r = wave * kRowsW + t * 8 + rsub;
-        const int kc = pos ^ ((r >> 1) & 7);
-        const int row = n0 + r < n_tokens ? n0 + r : n_tokens - 1;
-        load_lds16(X + (size_t)row * d_in + k0 + kc * 8, lds_addr(stage + (wave * kRowsW + t * 8) * BK));
-      }
-    } else {                                       // the ragged last step: zero past d_in
-#pragma unroll
-      for (int t = 0; t < kXLoads; ++t) {
-        const int r = wave * kRowsW + t * 8 + rsub;
-        const int kc = pos ^ ((r >> 1) & 7);
-        const int row = n0 + r;
-        uint16_t* base = stage + (wave * kRowsW + t * 8) * BK;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (row < n_tokens && k0 + kc * 8 < d_in) v = *(const uint4*)(X + (size_t)row * d_in + k0 + kc * 8);
-        *(uint4*)(base + lane * 8) = v;
-      }
-    }
-  };
-  const int wm = wave >> 1, wn = wave & 1;         // tokens 64 wm .., weight rows 64 wn ..
-  f32x16_t acc[MA][NBB];
-#pragma unroll
-  for (int a = 0; a < MA; ++a)
-#pragma unroll
-    for (int b = 0; b < NBB; ++b)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
-  struct Frags { bf16x8_t a[MA], b[NBB]; };
-  auto read_frags = [&](const uint16_t* xst, const uint16_t* bsl, int i, Frags& f) {
-#pragma unroll
-    for (int b = 0; b < NBB; ++b) f.b[b] = *(const bf16x8_t*)(bsl + ((wn * NBB + b) * 4 + i) * gemm::kChunk + lane * 8);
-    const int kc = 2 * i + half;
-#pragma unroll
-    for (int a = 0; a < MA; ++a) {
-      const int r = wm * 64 + a * 32 + r32;
-      f.a[a] = *(const bf16x8_t*)(xst + r * BK + ((kc ^ ((r >> 1) & 7)) * 8));
-    }
-  };
-  auto mfmas = [&](const Frags& f) {
-#pragma unroll
-    for (int a = 0; a < MA; ++a)
-#pragma unroll
-      for (int b = 0; b < NBB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[a], f.b[b], acc[a][b], 0, 0, 0);
-  };
-  for (int seq = 0; seq < kDepth - 1 && seq < nsteps; ++seq) load_stage(seq);
-  for (int seq = 0; seq < nsteps; ++seq) {
-    {                                              // own loads of step seq done (step seq + 1's may be out)
-      const int after = min(kDepth - 2, nsteps - 1 - seq);
-      if (after >= 1) wait_vmcnt<kLoads>(); else wait_vmcnt<0>();
-    }
-    __syncthreads();                               // stage seq published; stage seq - 1 free
-    if (seq + kDepth - 1 < nsteps) load_stage(seq + kDepth - 1);
-    const uint16_t* xst = S + (seq % kDepth) * kStage;
-    const uint16_t* bsl = xst + kXStage;
-    Frags f0, f1;
-    read_frags(xst, bsl, 0, f0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      Frags& cur = (i & 1) ? f1 : f0;
-      Frags& nxt = (i & 1) ? f0 : f1;
-      if (i < 3) read_frags(xst, bsl, i + 1, nxt);
-      mfmas(cur);
-      if (i < 3) {
-        __builtin_amdgcn_sched_group_barrier(0x100, MA + NBB, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, NBB * MA, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#pragma unroll
-  for (int b = 0; b < NBB; ++b) {
-    const int col = i0 + wn * 64 + b * 32 + r32;
-    if (col >= d_out) continue;
-    const float scale = f16_to_f32(scales[col]);
-#pragma unroll
-    for (int a = 0; a < MA; ++a) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = n0 + wm * 64 + a * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-        if (row < n_tokens) OutT<YDT>::store(Y, (size_t)row * d_out + col, acc[a][b][e] * scale);
-      }
-    }
-  }
-}
-
-// Pass 2 for problems with many tiles: 256 tokens x 256 weight rows per workgroup, 8 waves of 128 x 64
-// (4 x 2 MFMA blocks). Against the 256 x 128 tiles a step's LDS reads halve per product (each wave
-// reads 6 fragments for 8 MFMAs instead of 4 for 4), so the step is bound by the MFMAs; a stage (64
-// inputs, 64 KiB) is twice as long, so two stages suffice: the next one is loaded, by direct
-// global->LDS loads, while the current one is used, with one barrier per step. Both 128-row halves start
-// their K walk where gemm_kernel's column blocks do: same products in the same order.
-namespace gemm3 {
-constexpr int kWaves = 8, kThreads = 64 * kWaves, BM = 256, BN = 256, BK = 64;
-constexpr int kXStage = BM * BK, kStage = kXStage + BN * BK;   // bf16 values
-}  // namespace gemm3
-
-template <int YDT>
-__global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const uint16_t* __restrict__ Wt,
-                                                                       const uint16_t* __restrict__ scales,
-                                                                       const uint16_t* __restrict__ X, void* __restrict__ Y,
-                                                                       int n_tokens, int d_out, int d_in, int nsteps,
-                                                                       int n_tb, int n_cb, int n_c32) {
-  using namespace gemm3;
-  constexpr int MA = 4, NBB = 2;                   // 32 x 32 blocks per wave: 4 token x 2 weight row
+template <int YDT, int BN>
+__global__ __launch_bounds__(Dense<BN>::kThreads) void gemm_dense_kernel(const uint16_t* __restrict__ Wt,
+                                                                        const uint16_t* __restrict__ scales,
+                                                                        const uint16_t* __restrict__ X, void* __restrict__ Y,
+                                                                        int n_tokens, int d_out, int d_in, int nsteps,
+                                                                        int n_tb, int n_cb, int n_c32, int stagger) {
+  using D = Dense<BN>;
+  constexpr int BM = D::BM, BK = D::BK, kDepth = D::kDepth, MA = D::MA, NBB = D::NBB, kXStage = D::kXStage, kStage = D::kStage;
+  constexpr int kLoads = D::kXLoads + D::kWLoads;
   extern __shared__ uint4 smem3[];
   uint16_t* S = (uint16_t*)smem3;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -549,6 +419,7 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
   const int gw = n_tb - 4 * grp < 4 ? n_tb - 4 * grp : 4;
   const int cb = gt / gw, tb = 4 * grp + gt % gw;
   const int n0 = tb * BM, i0 = cb * BN;
+  const int s0 = stagger ? (int)(((long long)cb * nsteps) / n_cb) : 0;
 
   // This lane's four X pieces of a stage as offsets from the tile's first token (rows past the last
   // token read it again, never stored), and the wave's four weight chunks.
@@ -561,16 +432,23 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
     const uint32_t r = wave * 32 + q * 8 + rsub;
     xoff[q] = (r < last ? r : last) * row_b + (pos ^ ((r >> 1) & 7)) * 16;
   }
-  int c32 = i0 / 32 + wave;                        // the wave loads the four K-blocks of one 32-row block
-  if (c32 >= n_c32) c32 = n_c32 - 1;               // rows past d_out: any valid tile, never stored
-  const char* Wc = (const char*)(Wt + (size_t)c32 * nsteps * 4 * gemm::kChunk);
-  const uint32_t woff = lane * 16;
-  auto load_stage = [&](int st) {
-    uint16_t* stage = S + (st & 1) * kStage;
-    const char* wsrc = Wc + (size_t)st * 4 * gemm::kChunk * 2;
+  const char* Wc[D::kWLoads];                      // chunk c of a stage: 32-row block c / 4, K-block c % 4
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      load_lds16_off(wsrc + q * gemm::kChunk * 2, woff, lds_addr(stage + kXStage + (wave * 4 + q) * gemm::kChunk));
+  for (int q = 0; q < D::kWLoads; ++q) {
+    const int c = wave * D::kWLoads + q;
+    int c32 = i0 / 32 + (c >> 2);
+    if (c32 >= n_c32) c32 = n_c32 - 1;             // rows past d_out: any valid tile, never stored
+    Wc[q] = (const char*)(Wt + ((size_t)c32 * nsteps * 4 + (c & 3)) * gemm::kChunk);
+  }
+  const uint32_t woff = lane * 16;
+  auto stage_of = [&](int seq) { return S + (seq % kDepth) * kStage; };
+  auto load_stage = [&](int seq) {
+    const int st = s0 + seq >= nsteps ? s0 + seq - nsteps : s0 + seq;
+    uint16_t* stage = stage_of(seq);
+#pragma unroll
+    for (int q = 0; q < D::kWLoads; ++q)
+      load_lds16_off(Wc[q] + (size_t)st * 4 * gemm::kChunk * 2, woff,
+                     lds_addr(stage + kXStage + (wave * D::kWLoads + q) * gemm::kChunk));
     const char* xsrc = Xt + (size_t)st * BK * 2;
     if (st * BK + BK <= d_in) {
 #pragma unroll
@@ -585,7 +463,7 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
       }
     }
   };
-  const int wm = wave >> 2, wn = wave & 3;         // tokens 128 wm .., weight rows 64 wn ..
+  const int wm = wave / D::kWN, wn = wave % D::kWN;   // tokens 32 MA wm .., weight rows 64 wn ..
   f32x16_t acc[MA][NBB];
 #pragma unroll
   for (int a = 0; a < MA; ++a)
@@ -601,7 +479,7 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
     const int kc = 2 * i + half;
 #pragma unroll
     for (int a = 0; a < MA; ++a) {
-      const int r = wm * 128 + a * 32 + r32;
+      const int r = wm * 32 * MA + a * 32 + r32;
       f.a[a] = *(const bf16x8_t*)(xst + r * BK + ((kc ^ ((r >> 1) & 7)) * 8));
     }
   };
@@ -617,18 +495,24 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, MA * NBB - MA - NBB, 0);
+    if (MA * NBB > MA + NBB) __builtin_amdgcn_sched_group_barrier(0x008, MA * NBB - MA - NBB, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // Waits until this wave's loads of the stage needed next have landed (the later stages' may be out).
+  auto wait_stage = [&](bool later) {
+    if (kDepth == 3 && later) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kLoads) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  };
   load_stage(0);
-  wait_vmcnt<0>();
+  if (kDepth == 3 && nsteps > 1) load_stage(1);
+  wait_stage(nsteps > 1);
   __syncthreads();
-  if (nsteps > 1) load_stage(1);
+  if (kDepth - 1 < nsteps) load_stage(kDepth - 1);
   Frags f0, f1;
-  read_frags(S, 0, f0);
+  read_frags(stage_of(0), 0, f0);
   __builtin_amdgcn_sched_barrier(0);
-  for (int st = 0; st < nsteps; ++st) {
-    const uint16_t* xst = S + (st & 1) * kStage;
+  for (int seq = 0; seq < nsteps; ++seq) {
+    const uint16_t* xst = stage_of(seq);
     read_frags(xst, 1, f1);
     mfmas(f0);
     interleave();
@@ -638,13 +522,12 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
     read_frags(xst, 3, f1);
     mfmas(f0);
     interleave();
-    // Every fragment of this stage is in registers (of this wave, then of all): its buffer is free
-    // for the stage after next, and the next stage's first fragments are read under the last products.
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    // Every fragment of this stage is in registers (of this wave, then of all): its buffer is free.
+    wait_stage(seq + 2 < nsteps);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (st + 2 < nsteps) load_stage(st + 2);
-    if (st + 1 < nsteps) read_frags(S + ((st + 1) & 1) * kStage, 0, f0);
+    if (seq + kDepth < nsteps) load_stage(seq + kDepth);
+    if (seq + 1 < nsteps) read_frags(stage_of(seq + 1), 0, f0);
     mfmas(f1);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -657,7 +540,7 @@ __global__ __launch_bounds__(gemm3::kThreads) void gemm_dense256_kernel(const ui
     for (int a = 0; a < MA; ++a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int row = n0 + wm * 128 + a * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+        const int row = n0 + wm * 32 * MA + a * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
         if (row < n_tokens) OutT<YDT>::store(Y, (size_t)row * d_out + col, acc[a][b][e] * scale);
       }
     }
@@ -700,9 +583,9 @@ static double gemm_rounds(const Layer& L, int n_tokens, int bm, int bn) {
 // (8192 x 4096 x 4096, one pass, k = 1: 285 -> 269 us; 4096 tokens x 4096 x 11008: 381 -> 344 us).
 static bool gemm_dense256(const Layer& L, int n_tokens) {
   if (gemm_tile(L, n_tokens, -1) != 0 || L.d.d_in > (1 << 20)) return false;
-  const long long wg = (long long)((n_tokens + gemm2::BM - 1) / gemm2::BM) * ((L.d.d_out + gemm2::BN - 1) / gemm2::BN);
+  const long long wg = (long long)((n_tokens + 255) / 256) * ((L.d.d_out + 127) / 128);
   if (wg < (L.n_cu > 0 ? L.n_cu : 256)) return false;
-  return 116.0 * gemm_rounds(L, n_tokens, gemm3::BM, gemm3::BN) < 68.5 * gemm_rounds(L, n_tokens, gemm2::BM, gemm2::BN);
+  return 116.0 * gemm_rounds(L, n_tokens, 256, 256) < 68.5 * gemm_rounds(L, n_tokens, 256, 128);
 }
 
 template <int K, int CB, int BMT, int BNT, int CW>
@@ -780,15 +663,15 @@ hipError_t launch_gemm(const Layer& L, int k, const void* X, int n_tokens, void*
 size_t gemm_two_pass_bytes(const Layer& L, int k, int n_tokens) {
   if (L.d.code_bits != 8 && L.d.code_bits != 4) return 0;
   if (gemm_tile(L, n_tokens, -1) != 0) return 0;
-  const long long wg = (long long)((n_tokens + gemm2::BM - 1) / gemm2::BM) * ((L.d.d_out + gemm2::BN - 1) / gemm2::BN);
+  const long long wg = (long long)((n_tokens + 255) / 256) * ((L.d.d_out + 127) / 128);
   if (wg < (L.n_cu > 0 ? L.n_cu : 256)) return 0;
   if (k < 3) {
     if (!gemm_dense256(L, n_tokens)) return 0;
-    const double len = L.d.d_in / 4096.0, one = (k == 1 ? 70.0 : 76.0) * len * gemm_rounds(L, n_tokens, gemm2::BM, gemm2::BN);
-    const double two = 2.0 + 9.0 * len * L.d.d_out / 4096.0 + 116.0 * len * gemm_rounds(L, n_tokens, gemm3::BM, gemm3::BN);
+    const double len = L.d.d_in / 4096.0, one = (k == 1 ? 70.0 : 76.0) * len * gemm_rounds(L, n_tokens, 256, 128);
+    const double two = 2.0 + 9.0 * len * L.d.d_out / 4096.0 + 116.0 * len * gemm_rounds(L, n_tokens, 256, 256);
     if (two > 0.97 * one) return 0;
   }
-  const size_t n_c32 = (L.d.d_out + 31) / 32, nsteps = (L.d.d_in + gemm2::BK - 1) / gemm2::BK;
+  const size_t n_c32 = (L.d.d_out + 31) / 32, nsteps = (L.d.d_in + gemm::BK - 1) / gemm::BK;
   return n_c32 * nsteps * 4 * gemm::kChunk * 2;
 }
 
@@ -808,10 +691,22 @@ static void launch_wtile_k(const Layer& L, uint16_t* Wt, int n_c32, int nsteps, 
   else launch_wtile<K, 8>(L, Wt, n_c32, nsteps, st);
 }
 
+template <int BN>
+static void launch_dense(const Layer& L, const uint16_t* Wt, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
+                         int nsteps, int n_c32, int stagger, hipStream_t st) {
+  const int n_tb = (n_tokens + 255) / 256, n_cb = (L.d.d_out + BN - 1) / BN;
+  const size_t lds = (size_t)Dense<BN>::kDepth * Dense<BN>::kStage * 2;
+  if (y_dtype == AQMB_BF16)
+    gemm_dense_kernel<AQMB_BF16, BN><<<n_tb * n_cb, Dense<BN>::kThreads, lds, st>>>(
+        Wt, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, nsteps, n_tb, n_cb, n_c32, stagger);
+  else
+    gemm_dense_kernel<AQMB_F32, BN><<<n_tb * n_cb, Dense<BN>::kThreads, lds, st>>>(
+        Wt, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, nsteps, n_tb, n_cb, n_c32, stagger);
+}
+
 hipError_t launch_gemm_two_pass(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                                 void* workspace, hipStream_t st) {
-  using namespace gemm2;
-  const int n_c32 = (L.d.d_out + 31) / 32, nsteps = (L.d.d_in + BK - 1) / BK;
+  const int n_c32 = (L.d.d_out + 31) / 32, nsteps = (L.d.d_in + gemm::BK - 1) / gemm::BK;
   uint16_t* Wt = (uint16_t*)workspace;
   switch (k) {
     case 1: launch_wtile_k<1>(L, Wt, n_c32, nsteps, st); break;
@@ -823,31 +718,8 @@ hipError_t launch_gemm_two_pass(const Layer& L, int k, const void* X, int n_toke
     case 7: launch_wtile_k<7>(L, Wt, n_c32, nsteps, st); break;
     default: launch_wtile_k<8>(L, Wt, n_c32, nsteps, st); break;
   }
-  if (gemm_dense256(L, n_tokens)) {
-    const int n_tb = (n_tokens + gemm3::BM - 1) / gemm3::BM, n_cb = (L.d.d_out + gemm3::BN - 1) / gemm3::BN;
-    const size_t lds = (size_t)2 * gemm3::kStage * 2;
-    if (y_dtype == AQMB_BF16)
-      gemm_dense256_kernel<AQMB_BF16><<<n_tb * n_cb, gemm3::kThreads, lds, st>>>(Wt, L.scales, (const uint16_t*)X, Y, n_tokens,
-                                                                               L.d.d_out, L.d.d_in, nsteps, n_tb, n_cb, n_c32);
-    else
-      gemm_dense256_kernel<AQMB_F32><<<n_tb * n_cb, gemm3::kThreads, lds, st>>>(Wt, L.scales, (const uint16_t*)X, Y, n_tokens,
-                                                                              L.d.d_out, L.d.d_in, nsteps, n_tb, n_cb, n_c32);
-    return hipGetLastError();
-  }
-  const int n_tb = (n_tokens + BM - 1) / BM, n_cb = (L.d.d_out + BN - 1) / BN;
-  // XCD blocks: token tiles in ga groups, column blocks in gb groups, ga * gb = 8
-  int ga = 0, gb = 0;
-  const int cand[4][2] = {{2, 4}, {1, 8}, {4, 2}, {8, 1}};
-  for (const auto& c : cand)
-    if (n_tb % c[0] == 0 && n_cb % c[1] == 0) { ga = c[0]; gb = c[1]; break; }
-  const size_t lds = (size_t)kDepth * kStage * 2;
-  const dim3 grid(n_tb * n_cb);
-  if (y_dtype == AQMB_BF16)
-    gemm_dense_kernel<AQMB_BF16><<<grid, kThreads, lds, st>>>(Wt, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out,
-                                                             L.d.d_in, nsteps, n_tb, n_cb, n_c32, ga, gb);
-  else
-    gemm_dense_kernel<AQMB_F32><<<grid, kThreads, lds, st>>>(Wt, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out,
-                                                            L.d.d_in, nsteps, n_tb, n_cb, n_c32, ga, gb);
+  if (gemm_dense256(L, n_tokens)) launch_dense<256>(L, Wt, X, n_tokens, Y, y_dtype, nsteps, n_c32, 0, st);
+  else launch_dense<128>(L, Wt, X, n_tokens, Y, y_dtype, nsteps, n_c32, 1, st);
   return hipGetLastError();
 }
 

@@ -142,3 +142,27 @@ def test_quantlinear_takes_the_workspace_path():
     lin._workspace = lambda k, n, device: None
     assert torch.equal(lin(X, 3), one)
     lin.close()
+
+
+@pytest.mark.parametrize("d_out,d_in,n,ks", [
+    (4096, 512, 4096, (1, 2, 4)),      # one round of 256 x 256 tiles
+    (3900, 1000, 4000, (1, 3)),        # ragged rows (a 32-row block half empty), tokens and inputs
+    (8192, 64, 2048, (2,)),            # a single step
+    (5000, 136, 3400, (4,)),           # three steps, the last with one group; 14 token tiles (ragged XCD groups)
+])
+def test_dense_256_tiles(d_out, d_in, n, ks):
+    """The dense pass on 256 x 256 tiles: bit-identical to aqmb_gemm, and the oracle on sampled tokens."""
+    L = make_layer(LayerSpec("d256", d_out, d_in, M=max(ks), seed=310 + n))
+    Xbits = make_activations(L, n, "bf16", heavy_tail=True)
+    X, Xv = to_dev(Xbits).view(torch.bfloat16), act_values(Xbits, "bf16")
+    rows = np.r_[0:16, n // 2:n // 2 + 16, n - 16:n]
+    with GpuLayer(L.codes, L.codebooks, L.scales) as gl:
+        for k in ks:
+            nb = A.gemm_workspace_bytes(gl.handle, k, n)
+            if nb == 0:                                    # (k <= 2: only where two passes are estimated faster)
+                assert k < 3
+                continue
+            ws = torch.full((nb // 2,), 0x7FC0, dtype=torch.int16, device="cuda")
+            got = _run(gl, k, X, n, "bf16", ws)
+            assert np.array_equal(got, _run(gl, k, X, n, "bf16", False)), (d_out, d_in, n, k)
+            check_close(got[rows], oracle.gemm_reference(Xv[rows], L.codes, L.codebooks, L.scales, k), "bf16", f"k={k}")
