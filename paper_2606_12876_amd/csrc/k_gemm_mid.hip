@@ -16,7 +16,7 @@
 // large tiles leave compute units idle below about 2000 tokens and gather each weight from one
 // unreplicated codebook copy behind a barrier per 64 inputs. Measured (4096 x 4096, k = 4): 64 tokens
 // 23.0 -> 13.3 us, 150: 52.1 -> 20.1, 512: 53 -> 34, 1024: 76 -> 61; 11008 x 4096, k = 3, 333 tokens:
-// 75 -> 66 us; 3000 x 11008, k = 2, 100 tokens: 75 -> 22 us. Bound: at few tokens the start and end
+// 75 -> 58 us; 3000 x 11008, k = 2, 100 tokens: 75 -> 22 us. Bound: at few tokens the start and end
 // (about 6 us), then X through the CU's L2 port (16 tokens of 4096 inputs in 1.2-1.6 us, two thirds of
 // the full-line rate); on the 48- and 64-row tiles the LDS pipe (unit writes and reads beside the
 // codeword gathers). Sixteen waves instead of eight: 14.5 -> 13.1 us at 64 tokens, 30 -> 24 us at 100
@@ -39,7 +39,7 @@ template <int K, int RB> constexpr int code_loads() { return (RB * 16 * K + 63) 
 // Codebook copies: as many as fit beside the rings (16-codeword books fill the banks once: one).
 template <int K, int CB, int RB, int NB> constexpr int nrep() {
   if (CB == 4) return 1;
-  const int room = kLds - n_waves<RB, NB>() * (depth<RB, NB>() * kUnit + code_loads<K, RB>() * 1024) - 512;
+  const int room = kLds - n_waves<RB, NB>() * (depth<RB, NB>() * kUnit + code_loads<K, RB>() * 1024);
   return room >= K * 4096 * 8 ? 8 : room >= K * 4096 * 4 ? 4 : room >= K * 4096 * 2 ? 2 : 1;
 }
 template <int K, int CB, int RB, int NB> constexpr size_t lds_bytes() {
@@ -294,7 +294,10 @@ static hipError_t launch_shape(Args& a, int rb, int nb_max, hipStream_t st) {
   switch (rb * 100 + nb_max) {
     case 102: return launch<K, CB, 1, 2>(a, st);
     case 104: return launch<K, CB, 1, 4>(a, st);
+    case 202: return launch<K, CB, 2, 2>(a, st);
     case 204: return launch<K, CB, 2, 4>(a, st);
+    case 304: return launch<K, CB, 3, 4>(a, st);
+    case 312: return launch<K, CB, 3, 12>(a, st);
     case 208: return launch<K, CB, 2, 8>(a, st);
     case 308: return launch<K, CB, 3, 8>(a, st);
     default: return launch<K, CB, 4, 8>(a, st);
@@ -303,22 +306,25 @@ static hipError_t launch_shape(Args& a, int rb, int nb_max, hipStream_t st) {
 }  // namespace gmid
 
 // Tile choice: rows rb and token blocks nb (tokens spread evenly over the n_tt token tiles) with the
-// least estimated time, rounds of workgroups (one per compute unit) times a tile's time: 4.5 us of
-// start and end, 0.65 us per plane and 16 rows (dequantization), 0.9 + 0.2 rb us per token block (X
-// and the products) and 0.1 us per accumulator tile added at the end (fitted on 4096-input layers:
-// 9.8 / 13.1 us at 17 / 64 tokens, k = 4; 30.8 us for rb = 4, nb = 8).
+// least estimated time, rounds of workgroups (one per compute unit) times a tile's time on a
+// 4096-input layer: start and end, per plane and 16 rows (dequantization), per token block (X and the
+// products), fitted per shape (8-bit codes; us measured at one full round: 16 x 64 tokens 11.0 at k = 1
+// and 13.2 at k = 4, 32 x 32 8.9 and 14.5, 32 x 128 17.3 and 22.6, 48 x 64 13.5 and 22.1, 48 x 192 35.5 at
+// k = 4, 64 x 128 25.0 and 32.8).
 struct MidTile { int rb, nb_max, nb, n_tt; double us; };
 static MidTile mid_tile(const Layer& L, int k, int n) {
-  static const int shapes[6][2] = {{1, 2}, {1, 4}, {2, 4}, {2, 8}, {3, 8}, {4, 8}};
+  static const struct { int rb, nb; double start, plane, block; } shapes[9] = {
+      {1, 2, 5.3, 0.73, 1.0}, {1, 4, 6.0, 0.73, 1.0},  {2, 2, 4.8, 0.9, 1.15},
+      {2, 4, 5.6, 0.78, 1.2}, {2, 8, 5.0, 0.82, 1.4},  {3, 4, 5.2, 0.95, 1.35},
+      {3, 8, 8.0, 0.63, 1.42}, {3, 12, 9.0, 0.65, 1.53}, {4, 8, 8.0, 0.65, 1.75}};
   const int ncu = L.n_cu > 0 ? L.n_cu : 256, blocks = (n + 15) / 16;
   const double len = L.d.d_in / 4096.0;
   MidTile best{};
   for (const auto& s : shapes) {
-    const int tt = (blocks + s[1] - 1) / s[1], b = (blocks + tt - 1) / tt;
-    const long long wgs = (long long)((L.d.d_out + 16 * s[0] - 1) / (16 * s[0])) * tt;
-    const double us = (double)((wgs + ncu - 1) / ncu) *
-                      (4.5 + len * (0.65 * s[0] * k + (0.9 + 0.2 * s[0]) * b) + 0.1 * s[0] * s[1]);
-    if (best.rb == 0 || us < best.us) best = {s[0], s[1], b, tt, us};
+    const int tt = (blocks + s.nb - 1) / s.nb, b = (blocks + tt - 1) / tt;
+    const long long wgs = (long long)((L.d.d_out + 16 * s.rb - 1) / (16 * s.rb)) * tt;
+    const double us = (double)((wgs + ncu - 1) / ncu) * (s.start + len * (s.plane * s.rb * k + s.block * b));
+    if (best.rb == 0 || us < best.us) best = {s.rb, s.nb, b, tt, us};
   }
   return best;
 }

@@ -29,6 +29,9 @@ from gpu_helpers import GpuLayer, out_values, check_close, to_dev, TORCH_DT, A_D
     (8200, 136, 250, 8, (1,)),         # 48- and 64-row tiles
     (12300, 64, 130, 4, (3,)),
     (2050, 1160, 700, 8, (4,)),        # several token tiles of uneven size
+    (4090, 264, 50, 8, (1, 2)),        # 32 x 32 tiles, the last with two tokens
+    (11000, 200, 61, 8, (1, 3)),       # 48 x 64 tiles
+    (11010, 328, 185, 4, (2, 4)),      # 48 x 192 tiles
 ])
 def test_tile_edges(d_out, d_in, n, B, ks):
     L = make_layer(LayerSpec("mid", d_out, d_in, M=max(ks), B=B, seed=700 + n))
