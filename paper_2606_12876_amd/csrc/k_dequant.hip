@@ -133,166 +133,63 @@ __device__ __forceinline__ uint32_t code_x16(uint32_t w, int j) {
   return d;
 }
 
-// Used for 16-bit and 4-bit codes (and as the general fallback). CB = code bits. One thread per
-// group: the J = 128 / CB lanes of a (row, slice) pair take its J groups, so a wave writes whole
-// row segments (J groups x 8 values) and the lanes of one row share one 16-byte code chunk per
-// plane (a single cache line). 16- and 256-entry codebooks are staged in LDS; 65536-entry
-// codebooks are read through the caches.
-template <int OUT, int CB>
-__global__ __launch_bounds__(256) void dequant_kernel(const unsigned char* __restrict__ codes,
-                                                      const uint16_t* __restrict__ codebooks,
-                                                      const uint16_t* __restrict__ scales, void* __restrict__ W,
-                                                      int d_out, int d_in, int G, int S, int k, size_t plane_bytes) {
-  constexpr int J = 128 / CB, PER_WORD = 32 / CB;
-  extern __shared__ uint4 cb_lds[];  // [k][2^CB] codewords (CB <= 8)
+// Small layers: one thread per group (J = 128 / CB lanes for the groups of a (slice, row) pair), all of them
+// running at once. Bound: the latency of one chain - codebooks and code word in flight together, gather,
+// fold, store - against which the pieces of rows that a store instruction writes here do not count. 512 x 512,
+// k = 1 / 4, us (an empty kernel of that size: 2.3): 8-bit codes to bf16 3.8 / 4.8 -> 2.3 / 2.4, 4-bit codes
+// 4.7 / 5.5 -> 2.3 / 2.4; 16-bit codes, 2048 x 2048 to bf16, k = 1 / 2, 7.0 / 8.3 -> 5.1 / 7.0.
+template <int OUT, int CB, int K>
+__global__ __launch_bounds__(256) void dequant_small_kernel(const unsigned char* codes, const uint16_t* codebooks,
+                                                            const uint16_t* scales, void* W, int d_out, int d_in, int G,
+                                                            uint32_t nslot, size_t plane_bytes) {
+  constexpr int NCW = 1 << CB, J = 128 / CB, PER_WORD = 32 / CB;
+  __shared__ uint4 cbs[CB <= 8 ? K * NCW : 1];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (CB == 8) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) load_lds16((const uint4*)codebooks + i * 256 + tid, lds_addr(cbs + i * 256 + wave * 64));
+  } else if constexpr (CB == 4) {
+    if (tid < K * NCW) cbs[tid] = ((const uint4*)codebooks)[tid];
+  }
+  uint32_t slot = blockIdx.x * 256 + tid;
+  const bool live = slot < nslot;
+  slot = live ? slot : nslot - 1;                      // past the end: the last slot again, not stored
+  const uint32_t pair = slot / J, jj = slot % J, slice = pair / (uint32_t)d_out;
+  const int row = (int)(pair - slice * (uint32_t)d_out), grp = (int)(slice * J + jj);
+  const float scale = f16_to_f32(scales[row]);
+  uint32_t w[K];
+#pragma unroll
+  for (int m = 0; m < K; ++m) w[m] = *(const uint32_t*)(codes + m * plane_bytes + (size_t)pair * 16 + jj / PER_WORD * 4);
   if constexpr (CB <= 8) {
-    for (int q = threadIdx.x; q < (k << CB); q += blockDim.x) cb_lds[q] = ((const uint4*)codebooks)[q];
+    wait_vmcnt<0>();
     __syncthreads();
   }
-  // Each thread takes U groups per pass and issues all their code loads before using any.
-  constexpr int U = 4;
-  const size_t n = (size_t)S * d_out * J;
-  const size_t stride = (size_t)gridDim.x * blockDim.x * U;
-  for (size_t base = (size_t)blockIdx.x * blockDim.x * U + threadIdx.x; base < n; base += stride) {
-    uint32_t words[U][8];
-    int row[U], grp[U];
+  if (!live || grp >= G) return;
+  float acc[8];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t t = base + (size_t)u * blockDim.x;
-      const int jj = (int)(t % J);
-      const size_t pair = t / J;  // (slice, row) pair, rows fastest
-      row[u] = (int)(pair % d_out);
-      const int s = (int)(pair / d_out);
-      grp[u] = (t < n) ? s * J + jj : G;
-      const size_t chunk = pair * 16 + (size_t)(jj / PER_WORD) * 4;  // the code word holding this group
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        words[u][m] = 0;
-        if (m < k && grp[u] < G) words[u][m] = *(const uint32_t*)(codes + m * plane_bytes + chunk);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (grp[u] >= G) continue;
-      const int jj = grp[u] % J;
-      float acc[8];
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        if (m < k) {
-          uint4 cw;
-          const uint32_t code = (words[u][m] >> (CB * (jj % PER_WORD))) & ((1u << CB) - 1u);
-          if constexpr (CB <= 8) {
-            cw = cb_lds[(m << CB) + code];
-          } else {
-            cw = ((const uint4*)codebooks)[((size_t)m << 16) + code];
-          }
-          fold_codeword(acc, cw, m == 0);
-        }
-      }
-      const float scale = f16_to_f32(scales[row[u]]);
-      float w[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        w[e] = acc[e] * scale;
-        // Keep the binary32 product: without this the backend may fuse the multiply and the
-        // fp16 conversion into one mixed-precision instruction that rounds only once.
-        asm volatile("" : "+v"(w[e]));
-      }
-      store_group<OUT>(W, (size_t)row[u] * d_in + (size_t)grp[u] * 8, w);
-    }
+  for (int m = 0; m < K; ++m) {
+    const uint32_t code = (w[m] >> (CB * (jj % PER_WORD))) & (NCW - 1);
+    fold_codeword(acc, CB <= 8 ? cbs[m * NCW + code] : ((const uint4*)codebooks)[((size_t)m << 16) + code], m == 0);
   }
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    v[e] = acc[e] * scale;
+    asm volatile("" : "+v"(v[e]));                     // keep the binary32 product: no fused multiply and conversion
+  }
+  store_group<OUT>(W, (size_t)row * d_in + (size_t)grp * 8, v);
 }
 
-// 8-bit codes, K = k planes, thread per group: the 16 lanes of a (slice, row) pair take its 16
-// groups, so every store instruction of a wave writes four whole 256-byte row segments. Each
-// thread takes U groups per pass (slots t, t + 256, ...; U = 1 measured best) and passes are
-// grid-strided; the code
-// words and row scales of the next pass are requested before the current pass is folded, with
-// two register sets used in turn so that no copy waits for them. The codebooks go straight to
-// LDS and the first pass's code words are requested right behind them; loads complete in order,
-// so the wait for the codebooks does not wait for the code words. Code words are read once,
-// with a streaming hint. The pointers are deliberately not restrict-qualified: that would let
-// the compiler treat the loads as invariant and move them next to their uses.
-template <int OUT, int K>
-__global__ __launch_bounds__(256) void dequant8_kernel(const unsigned char* codes, const uint16_t* codebooks,
-                                                       const uint16_t* scales, void* W,
-                                                       int d_out, int d_in, int G, int S, size_t plane_bytes) {
-  constexpr int U = 1;
-  extern __shared__ uint4 cb8[];  // [K][256] codewords
-  // group slots fit in 32 bits (the launcher checks 16 S d_out < 2^30)
-  const uint32_t nslot = (uint32_t)S * (uint32_t)d_out * 16u;
-  const uint32_t stride = gridDim.x * blockDim.x * U;
-  uint32_t t = blockIdx.x * blockDim.x * U + threadIdx.x;
-  // code words (the 4-byte word holding each group's code, per plane) and row scales of the U
-  // slots of pass tt; slots past the end re-read the last slot and are not used
-  auto load = [&](uint32_t tt, uint32_t (&w)[U][K], uint32_t (&sc)[U]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      uint32_t slot = tt + u * blockDim.x;
-      slot = slot < nslot ? slot : nslot - 1;
-      const uint32_t pair = slot >> 4;
-      sc[u] = scales[pair % (uint32_t)d_out];
-#pragma unroll
-      for (int m = 0; m < K; ++m)
-        w[u][m] = __builtin_nontemporal_load(
-            (const uint32_t*)(codes + m * plane_bytes + (size_t)pair * 16 + (slot & 12)));
-    }
-  };
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-#pragma unroll
-  for (int i = 0; i < K; ++i)
-    load_lds16((const uint4*)codebooks + i * 256 + threadIdx.x, lds_addr(cb8 + i * 256 + wave * 64));
-  uint32_t wa[U][K], wb[U][K];
-  uint32_t sa[U], sb[U];                             // row scales (fp16 bits), one per register
-  load(t, wa, sa);
-  wait_vmcnt<U * (K + 1)>();
-  __syncthreads();
-  auto pass = [&](uint32_t tt, const uint32_t (&w)[U][K], const uint32_t (&sc)[U]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t slot = tt + u * blockDim.x;
-      const uint32_t pair = slot >> 4;
-      const uint32_t slice = pair / (uint32_t)d_out;
-      const int row = (int)(pair - slice * (uint32_t)d_out);
-      const int grp = (int)slice * 16 + (int)(slot & 15);
-      if (slot >= nslot || grp >= G) continue;
-      const int sh = 8 * (int)(slot & 3);
-      float acc[8];
-#pragma unroll
-      for (int m = 0; m < K; ++m) fold_codeword(acc, cb8[m * 256 + ((w[u][m] >> sh) & 0xFFu)], m == 0);
-      const float scale = f16_to_f32((uint16_t)sc[u]);
-      float v[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        v[e] = acc[e] * scale;
-        asm volatile("" : "+v"(v[e]));  // keep the binary32 product (see dequant_kernel)
-      }
-      store_group<OUT>(W, (size_t)row * d_in + (size_t)grp * 8, v);
-    }
-  };
-  for (; t < nslot; t += 2 * stride) {
-    load(t + stride, wb, sb);
-    __builtin_amdgcn_sched_barrier(0);
-    pass(t, wa, sa);
-    if (t + stride >= nslot) break;
-    load(t + 2 * stride, wa, sa);
-    __builtin_amdgcn_sched_barrier(0);
-    pass(t + stride, wb, sb);
-  }
-}
-
-// 8-bit codes, 16-bit output (f16 or bf16), K = k planes: tiles of RT rows x GT groups (RT GT =
-// 2048 or 4096 groups, 32 or 64 KiB of output), 512 threads. Thread t takes row t % RT of the tile
-// and P = RT GT / 512 consecutive groups of it (part (t / RT) of the tile's GT / 16 slices): one
-// P-byte code load per plane brings them, which it folds (same arithmetic and order as
-// dequant8_kernel) into the tile in LDS, row-major, its 16-byte chunks XOR-swizzled by row so that
-// both the column-wise writes and the row-wise reads hit every bank group. Then the waves write
-// the tile row by row, 1 KiB contiguous per store instruction (measured: 64 rows x 256-byte
-// pieces per instruction, the thread-per-group layout, is 20 % slower; rows written by one lane
-// each, 4x slower). Tiles are numbered column tiles fastest, so the tiles in flight together
-// cover whole rows of the output (a contiguous range of addresses). A workgroup walks its tiles
-// with the grid's stride; the code words of its next tile are requested before the current one is
-// folded.
+// 8-bit codes to 16 bits where codes and output together outgrow the last-level cache's reach (see
+// launch_dequant_k): tiles of RT rows x GT groups (RT GT = 2048 groups, 32 KiB of output), 512 threads.
+// Thread t takes row t % RT of the tile and P = RT GT / 512 consecutive groups of it (part (t / RT) of the
+// tile's GT / 16 slices): one P-byte code load per plane brings them, which it folds into the tile in LDS,
+// row-major, its 16-byte chunks XOR-swizzled by row so that both the column-wise writes and the row-wise
+// reads hit every bank group. Then the waves write the tile row by row, 1 KiB contiguous per store
+// instruction and P of them back to back, which HBM takes faster than the steady trickle of
+// dequant_kernel. Tiles are numbered column tiles fastest, so the tiles in flight together cover whole rows
+// of the output. A workgroup walks its tiles with the grid's stride; the code words of its next tile are
+// requested before the current one is folded.
 namespace dq {
 constexpr int kThreads = 512, kWaves = kThreads / 64;
 }
@@ -310,7 +207,7 @@ __global__ __launch_bounds__(dq::kThreads) void dequant8_tile_kernel(const unsig
                                                                     const uint16_t* scales, void* W, int d_out, int d_in,
                                                                     int G, int S, size_t plane_bytes) {
   static_assert(OUT == AQMB_F16 || OUT == AQMB_BF16, "16-bit outputs");
-  static_assert(RT * GT == 4096 || RT * GT == 2048, "tile size");
+  static_assert(RT * GT == 2048, "tile size");
   static_assert(GT >= 64 && (GT & (GT - 1)) == 0 && RT <= 64, "swizzle range");
   using namespace dq;
   constexpr int P = RT * GT / kThreads, kParts = 16 / P, ST = GT / 16, CP = GT / 64;
@@ -368,7 +265,7 @@ __global__ __launch_bounds__(dq::kThreads) void dequant8_tile_kernel(const unsig
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         v[e] = acc[e] * scale;
-        asm volatile("" : "+v"(v[e]));  // keep the binary32 product (see dequant_kernel)
+        asm volatile("" : "+v"(v[e]));  // keep the binary32 product: no fused multiply and conversion
       }
       const uint4 o = OUT == AQMB_F16
                           ? make_uint4(pack_f16x2(v[0], v[1]), pack_f16x2(v[2], v[3]), pack_f16x2(v[4], v[5]), pack_f16x2(v[6], v[7]))
@@ -389,95 +286,213 @@ __global__ __launch_bounds__(dq::kThreads) void dequant8_tile_kernel(const unsig
   }
 }
 
-// Tile shape and grid. Layers with at most two 64 KiB tiles per compute unit: one tile per
-// workgroup, as few rows and as many groups as the row length allows (8 x 512 for rows of 512
-// groups or more: a workgroup writes whole rows, one contiguous range); measured on the 4096 x 4096
-// layer, 8.6 / 8.8 / 9.5 / 10.0 us at k = 1..4 against 8.6 / 9.6 / 9.5 / 10.5 for 64 x 64 tiles.
-// Larger layers: 32 x 64 tiles and two workgroups per compute unit, each walking its tiles (on the
-// 11008 x 4096 layer 22 / 26 us at k = 1 / 4 against 25 / 29 for one 8 x 512 tile per workgroup).
-template <int OUT, int K>
-static void launch_dequant8_tile_k(const Layer& L, void* W, int n_cu, hipStream_t st) {
-  const int d_out = L.d.d_out;
-  auto n_tiles = [&](int rt, int gt) { return ((d_out + rt - 1) / rt) * ((L.S + gt / 16 - 1) / (gt / 16)); };
-  auto go = [&](auto kern, int grid) {
-    kern<<<(unsigned)std::min(grid, 65535), dq::kThreads, 0, st>>>(L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in,
-                                                                   L.G, L.S, L.plane_bytes);
+// Dequantization, every code width and output type. Bound: the stores of W (the codes are 1/16 to 1/4 of
+// them), and for 65536-entry codebooks the gathers of codewords through the L2.
+// A wave takes units of R rows x 64 groups. It loads the unit's code slices (per plane one load, R rows x
+// 16 bytes of each slice), turns them through its own LDS so that lane l finds the code of group l (fp32
+// output: of group l / 2, the lane making its half of the group), gathers and folds the codewords and
+// stores them: every store instruction writes 1 KiB of one row (64 rows x 256-byte pieces, which a lane
+// per group in code order gives, cost 2.5 x as much at fp32), and no wave waits for another after the
+// codebooks are staged. Units are numbered along the rows, so that the waves of a workgroup write whole
+// rows between them; the next unit's codes are requested before the current unit is folded. 16- and
+// 256-entry codebooks are staged in LDS, 65536-entry ones are read through the caches.
+// Measured on the 4096 x 11008 layer, us (fill of the same output: 15.0 at 16 bits, 28.2 at 32), before:
+// a kernel with a workgroup-wide output tile for 8-bit codes to 16 bits, a thread per group for the rest:
+//   8-bit codes   bf16 k = 1..4  20.8 22.5 24.2 26.6 -> 18.1 18.8 18.8 21.0   fp32  84 79 75 73 -> 35 36 37 39
+//   4-bit codes   bf16 k = 1..4  23.8                -> 18.1 18.3 18.8 19.0   fp32  84          -> 35 36 36 37
+//   16-bit codes  bf16 k = 1, 2  32.5 54.6           -> 32.9 52.7             fp32  66 72       -> 41 66
+template <int CB, int K, int R, int NW> constexpr size_t dequant_lds() {
+  return (CB <= 8 ? (size_t)K * (1 << CB) * 16 : 0) + (size_t)NW * K * R * 8 * CB;
+}
+
+template <int OUT, int CB, int K, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void dequant_kernel(const unsigned char* codes, const uint16_t* codebooks,
+                                                          const uint16_t* scales, void* W, int d_out, int d_in, int G, int S,
+                                                          size_t plane_bytes, int n_units, int n_ct) {
+  constexpr int NCW = 1 << CB, NSL = CB / 2, kRowB = 8 * CB;   // slices, code bytes of a unit's row
+  constexpr bool F32 = OUT == AQMB_F32;
+  extern __shared__ uint4 dequant_smem[];
+  uint4* cbs = dequant_smem;                           // [K][NCW] codewords (CB <= 8)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  unsigned char* buf = (unsigned char*)(dequant_smem + (CB <= 8 ? K * NCW : 0)) + wave * K * R * kRowB;
+  const int lr = lane % R, ls = lane / R;              // row and slice this lane loads (ls < NSL)
+  uint4 c[K];
+  uint32_t sc = 0;
+  auto load = [&](int u) {                             // units past the end reload the last one
+    u = u < n_units ? u : n_units - 1;
+    int row = (u / n_ct) * R + lr, sl = (u % n_ct) * NSL + ls;
+    row = row < d_out ? row : d_out - 1;
+    sl = sl < S ? sl : S - 1;
+    sc = scales[row];
+    if (ls < NSL) {
+#pragma unroll
+      for (int m = 0; m < K; ++m) c[m] = load_stream16(codes + m * plane_bytes + ((size_t)sl * d_out + row) * 16);
+    }
   };
-  if (n_cu > 0 && n_tiles(64, 64) > 2 * n_cu) {
-    go(dequant8_tile_kernel<OUT, K, 32, 64>, std::min(n_tiles(32, 64), 2 * n_cu));
-  } else if (L.G > 256) {
-    go(dequant8_tile_kernel<OUT, K, 8, 512>, n_tiles(8, 512));
-  } else if (L.G > 128) {
-    go(dequant8_tile_kernel<OUT, K, 16, 256>, n_tiles(16, 256));
-  } else if (L.G > 64) {
-    go(dequant8_tile_kernel<OUT, K, 32, 128>, n_tiles(32, 128));
+  int u = blockIdx.x * NW + wave;
+  if constexpr (CB == 8) {
+#pragma unroll
+    for (int q = 0; q < K * NCW / 64; q += NW)
+      if (q + wave < K * NCW / 64) load_lds16((const uint4*)codebooks + (q + wave) * 64 + lane, lds_addr(cbs + (q + wave) * 64));
+  } else if constexpr (CB == 4) {
+    if (tid < K * NCW) cbs[tid] = ((const uint4*)codebooks)[tid];
+  }
+  load(u);
+  if constexpr (CB <= 8) {
+    wait_vmcnt<0>();
+    __syncthreads();
+  }
+  const int gl = F32 ? lane >> 1 : lane;               // this lane's group of a row (fp32: of each half unit)
+  for (; u < n_units; u += gridDim.x * NW) {
+    const int r0 = (u / n_ct) * R, g0 = (u % n_ct) * 64;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the previous unit's code reads precede these writes
+    __builtin_amdgcn_wave_barrier();
+    if (ls < NSL) {
+#pragma unroll
+      for (int m = 0; m < K; ++m) *(uint4*)(buf + (m * R + lr) * kRowB + ls * 16) = c[m];
+    }
+    const uint32_t scales8 = sc;                       // lane r: the scale of row r0 + r
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    load(u + gridDim.x * NW);
+    auto get = [&](int r, int m, int g) -> uint32_t {
+      const unsigned char* p = buf + (m * R + r) * kRowB;
+      if constexpr (CB == 16) return ((const uint16_t*)p)[g];
+      else if constexpr (CB == 8) return p[g];
+      else return (p[g >> 1] >> (4 * (g & 1))) & 15u;
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      // 16-bit codes: the branch keeps the gathers of one row together (33.5 us, against 35.2 without it)
+      if (CB == 16 && r0 + r >= d_out) break;
+      const float scale = f16_to_f32(__builtin_amdgcn_readlane(scales8, r));
+#pragma unroll
+      for (int h = 0; h < (F32 ? 2 : 1); ++h) {
+        const int g = h * 32 + gl;
+        uint4 cw[K];
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+          const uint32_t code = get(r, m, g);
+          const uint4* src = CB <= 8 ? cbs + ((uint32_t)(m * NCW) + code)
+                                     : (const uint4*)codebooks + (((size_t)m << 16) + code);
+          if constexpr (F32) {
+            const uint2 v = ((const uint2*)src)[lane & 1];
+            cw[m] = make_uint4(v.x, v.y, 0u, 0u);
+          } else {
+            cw[m] = *src;
+          }
+        }
+        float acc[8];
+        if constexpr (K == 1) fold_codeword(acc, cw[0], true);
+        else fold_first_two(acc, cw[0], cw[K > 1 ? 1 : 0]);
+#pragma unroll
+        for (int m = 2; m < K; ++m) fold_codeword(acc, cw[m], false);
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < (F32 ? 4 : 8); ++e) {
+          v[e] = acc[e] * scale;
+          asm volatile("" : "+v"(v[e]));               // keep the binary32 product: no fused multiply and conversion
+        }
+        if (r0 + r >= d_out || g0 + g >= G) continue;
+        const size_t o = (size_t)(r0 + r) * d_in + (size_t)(g0 + g) * 8;
+        if constexpr (F32)
+          store_stream16((float*)W + o + 4 * (lane & 1), __float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
+                         __float_as_uint(v[3]));
+        else
+          store_group<OUT>(W, o, v);
+      }
+    }
+  }
+}
+
+// Which kernel. All times in us, this side of the line / the other, 256 compute units.
+// - A thread per group while all threads run at once (2048 per compute unit) and the output is 16 bits wide:
+//   2048 x 2048, 8-bit codes, k = 1 / 4: 3.8 / 4.4 against 3.9 / 4.7; 1500 x 3000, past the line, 5.5 / 6.1
+//   against 4.7 / 5.5. fp32 output stores twice as much in 32-byte pieces per thread: up to 640 threads per
+//   unit (1000 x 1032: 3.8 / 4.0 against 3.8 / 4.3; 333 x 8200: 6.0 / 6.3 against 4.9 / 5.7), with 16-bit
+//   codes, where the gathers take longer, 1536 (333 x 8200, k = 1 / 2: 6.3 / 6.9 against 7.7 / 9.1; 2048 x
+//   2048: 8.0 / 9.6 against 7.2 / 9.5).
+// - dequant8_tile_kernel, 8-bit codes to 16 bits, once codes and output pass 148 MiB: 14336 x 4096 is 34 / 37
+//   at k = 6 / 8 (154, 168 MiB) against 37 / 41, and 32 at k = 4 (140 MiB) against 29; 28672 x 8192 is 91 / 112
+//   at k = 1 / 4 against 100 / 122.
+// - dequant_kernel for the rest, with at most as many workgroups as run at once, each wave walking its units
+//   with the grid's stride. Codebooks in LDS: units of 8 rows where every wave gets one (8 per compute unit at
+//   k >= 3, 16 at k <= 2, where a unit is soon done: 4096 x 4096, 16 per unit, bf16, k = 1..4 is 11.2 9.3 9.0
+//   10.1 with 8 rows, 8.7 8.9 10.1 10.9 with 4), else of 4 rows; 4-wave workgroups where 8-wave ones would give
+//   a few compute units a second one (1500 x 3000, bf16, k = 4: 5.8 against 6.2) and, with 2 rows, where they
+//   would leave more than a quarter of the compute units idle (1000 x 1032: 3.3 against 3.6 at k = 2); at
+//   full load 8 waves share a codebook copy better (4096 x 11008, k = 3: 19.9 against 24.2).
+//   65536-entry codebooks: units of 8 rows (1500 x 3000, k = 1: 6.2 against 6.9 with 4), and 4-wave workgroups
+//   on large layers, which leave the compute unit one by one (4096 x 11008, k = 2: 52.7 against 55.3), 8-wave
+//   ones on small layers, where they keep to fewer compute units (1500 x 3000, k = 2: 9.0 against 9.7).
+template <int OUT, int CB, int K>
+static void launch_dequant_k(const Layer& L, void* W, hipStream_t st) {
+  const int d_out = L.d.d_out, ncu = L.n_cu > 0 ? L.n_cu : 256, n_ct = (L.G + 63) / 64;
+  const size_t nslot = (size_t)L.S * d_out * (128 / CB);
+  const int resident = OUT != AQMB_F32 ? 2048 : CB == 16 ? 1536 : 640;
+  if (nslot <= (size_t)resident * ncu) {
+    dequant_small_kernel<OUT, CB, K><<<(unsigned)((nslot + 255) / 256), 256, 0, st>>>(
+        L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in, L.G, (uint32_t)nslot, L.plane_bytes);
+    return;
+  }
+  if constexpr (CB == 8 && OUT != AQMB_F32) {
+    const size_t bytes = (size_t)d_out * L.d.d_in * 2 + K * L.plane_bytes;
+    if (bytes > ((size_t)148 << 20) && nslot < ((size_t)1 << 30)) {
+      const int n_tiles = ((d_out + 31) / 32) * ((L.S + 3) / 4);
+      dequant8_tile_kernel<OUT, K, 32, 64><<<std::min(n_tiles, 2 * ncu), dq::kThreads, 0, st>>>(
+          L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in, L.G, L.S, L.plane_bytes);
+      return;
+    }
+  }
+  auto go = [&](auto kern, size_t lds, int rows, int nw) {
+    const int n_units = n_ct * ((d_out + rows - 1) / rows);
+    const int per_cu = std::min<int>(160 * 1024 / (int)lds, 32 / nw);
+    const int grid = std::min((n_units + nw - 1) / nw, per_cu * ncu);
+    kern<<<grid, 64 * nw, lds, st>>>(L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in, L.G, L.S, L.plane_bytes, n_units,
+                                     n_ct);
+  };
+  const size_t u8 = (size_t)n_ct * ((d_out + 7) / 8), u4 = (size_t)n_ct * ((d_out + 3) / 4), cus = ncu;
+  if constexpr (CB == 16) {
+    if (u8 > (K <= 2 ? 16 : 8) * cus) go(dequant_kernel<OUT, 16, K, 8, 4>, dequant_lds<16, K, 8, 4>(), 8, 4);
+    else go(dequant_kernel<OUT, 16, K, 8, 8>, dequant_lds<16, K, 8, 8>(), 8, 8);
+  } else if (u8 > (K <= 2 ? 16 : 8) * cus) {
+    go(dequant_kernel<OUT, CB, K, 8, 8>, dequant_lds<CB, K, 8, 8>(), 8, 8);
+  } else if (u4 < 6 * cus) {
+    go(dequant_kernel<OUT, CB, K, 2, 4>, dequant_lds<CB, K, 2, 4>(), 2, 4);
+  } else if (u4 > 8 * cus && u4 < 12 * cus) {
+    go(dequant_kernel<OUT, CB, K, 4, 4>, dequant_lds<CB, K, 4, 4>(), 4, 4);
   } else {
-    go(dequant8_tile_kernel<OUT, K, 64, 64>, n_tiles(64, 64));
+    go(dequant_kernel<OUT, CB, K, 4, 8>, dequant_lds<CB, K, 4, 8>(), 4, 8);
+  }
+}
+
+template <int OUT, int CB>
+static void launch_dequant_cb(const Layer& L, int k, void* W, hipStream_t st) {
+  switch (k) {
+    case 1: launch_dequant_k<OUT, CB, 1>(L, W, st); break;
+    case 2: launch_dequant_k<OUT, CB, 2>(L, W, st); break;
+    case 3: launch_dequant_k<OUT, CB, 3>(L, W, st); break;
+    case 4: launch_dequant_k<OUT, CB, 4>(L, W, st); break;
+    case 5: launch_dequant_k<OUT, CB, 5>(L, W, st); break;
+    case 6: launch_dequant_k<OUT, CB, 6>(L, W, st); break;
+    case 7: launch_dequant_k<OUT, CB, 7>(L, W, st); break;
+    
+    default: launch_dequant_k<OUT, CB, 8>(L, W, st); break;
   }
 }
 
 template <int OUT>
-static void launch_dequant8_tile(const Layer& L, int k, void* W, int n_cu, hipStream_t st) {
-  switch (k) {
-    case 1: launch_dequant8_tile_k<OUT, 1>(L, W, n_cu, st); break;
-    case 2: launch_dequant8_tile_k<OUT, 2>(L, W, n_cu, st); break;
-    case 3: launch_dequant8_tile_k<OUT, 3>(L, W, n_cu, st); break;
-    case 4: launch_dequant8_tile_k<OUT, 4>(L, W, n_cu, st); break;
-    case 5: launch_dequant8_tile_k<OUT, 5>(L, W, n_cu, st); break;
-    case 6: launch_dequant8_tile_k<OUT, 6>(L, W, n_cu, st); break;
-    case 7: launch_dequant8_tile_k<OUT, 7>(L, W, n_cu, st); break;
-    default: launch_dequant8_tile_k<OUT, 8>(L, W, n_cu, st); break;
-  }
-}
-
-template <int OUT>
-static void launch_dequant8(const Layer& L, int k, void* W, unsigned grid, hipStream_t st) {
-  const size_t lds = (size_t)k * 256 * 16;
-  auto go = [&](auto kern) {
-    kern<<<grid, 256, lds, st>>>(L.codes, L.codebooks, L.scales, W, L.d.d_out, L.d.d_in, L.G, L.S, L.plane_bytes);
-  };
-  switch (k) {
-    case 1: go(dequant8_kernel<OUT, 1>); break;
-    case 2: go(dequant8_kernel<OUT, 2>); break;
-    case 3: go(dequant8_kernel<OUT, 3>); break;
-    case 4: go(dequant8_kernel<OUT, 4>); break;
-    case 5: go(dequant8_kernel<OUT, 5>); break;
-    case 6: go(dequant8_kernel<OUT, 6>); break;
-    case 7: go(dequant8_kernel<OUT, 7>); break;
-    default: go(dequant8_kernel<OUT, 8>); break;
-  }
+static void launch_dequant_out(const Layer& L, int k, void* W, hipStream_t st) {
+  if (L.d.code_bits == 8) launch_dequant_cb<OUT, 8>(L, k, W, st);
+  else if (L.d.code_bits == 4) launch_dequant_cb<OUT, 4>(L, k, W, st);
+  else launch_dequant_cb<OUT, 16>(L, k, W, st);
 }
 
 hipError_t launch_dequant(const Layer& L, int k, void* W, aqmb_dtype w_dtype, hipStream_t st) {
-  const size_t nslot = (size_t)L.S * L.d.d_out * 16;
-  if (L.d.code_bits == 8 && w_dtype != AQMB_F32 && nslot < ((size_t)1 << 30)) {
-    if (w_dtype == AQMB_F16) launch_dequant8_tile<AQMB_F16>(L, k, W, L.n_cu, st);
-    else launch_dequant8_tile<AQMB_BF16>(L, k, W, L.n_cu, st);
-    return hipGetLastError();
-  }
-  if (L.d.code_bits == 8 && nslot < ((size_t)1 << 30)) {
-    // fp32 output: one thread per group slot and pass; at most 2048 workgroups (eight per CU), so
-    // large layers take several passes and the reads of one overlap the writes of another
-    // (t + 2 * stride stays below 2^31)
-    const unsigned grid = (unsigned)std::max<size_t>(1, std::min<size_t>((nslot + 255) / 256, 2048));
-    launch_dequant8<AQMB_F32>(L, k, W, grid, st);
-    return hipGetLastError();
-  }
-  // 16- and 4-bit codes (and 8-bit layers too large for 32-bit thread indices): one thread per group
-  const size_t n = (size_t)L.S * L.d.d_out * L.J;
-  const unsigned grid = (unsigned)std::min<size_t>((n + 1023) / 1024, 2048);
-  const size_t lds = L.d.code_bits <= 8 ? ((size_t)k << L.d.code_bits) * 16 : 0;
-  auto go = [&](auto kern) {
-    kern<<<grid, 256, lds, st>>>(L.codes, L.codebooks, L.scales, W, L.d.d_out, L.d.d_in, L.G, L.S, k, L.plane_bytes);
-  };
-  auto pick = [&](auto f32, auto f16, auto bf16) {
-    if (w_dtype == AQMB_F32) go(f32);
-    else if (w_dtype == AQMB_F16) go(f16);
-    else go(bf16);
-  };
-  if (L.d.code_bits == 8) pick(dequant_kernel<AQMB_F32, 8>, dequant_kernel<AQMB_F16, 8>, dequant_kernel<AQMB_BF16, 8>);
-  else if (L.d.code_bits == 4) pick(dequant_kernel<AQMB_F32, 4>, dequant_kernel<AQMB_F16, 4>, dequant_kernel<AQMB_BF16, 4>);
-  else pick(dequant_kernel<AQMB_F32, 16>, dequant_kernel<AQMB_F16, 16>, dequant_kernel<AQMB_BF16, 16>);
+  if (w_dtype == AQMB_F32) launch_dequant_out<AQMB_F32>(L, k, W, st);
+  else if (w_dtype == AQMB_F16) launch_dequant_out<AQMB_F16>(L, k, W, st);
+  else launch_dequant_out<AQMB_BF16>(L, k, W, st);
   return hipGetLastError();
 }
 
