@@ -323,7 +323,7 @@ def main():
             for r in range(n_w):
                 A.dequant(hs2[r * 7], k, Ws[r], A.DType.BF16)
         ops.append(dict(name="dequant", shape=spec2.name, k=k, b=0, fn=fn, n=n_w,
-                        bytes=k * 4096 * 512 + k * 4096 + 2 * 4096 + 2 * 4096 * 4096, kernel="dequant_kernel"))
+                        bytes=k * 4096 * 512 + k * 4096 + 2 * 4096 + 2 * 4096 * 4096, kernel="dequant8_tile_kernel"))
 
     # prefill GEMM
     gspec = config("prefill")
@@ -516,7 +516,7 @@ def main():
                                            "frac": round(g4["tflops"] / ceil["mfma_bf16_random_TFLOPs"], 4)}
     out["gemm_TFLOPs"] = round(len(gemm) * gflop / (sum(o["us"] for o in gemm) * 1e-6) / 1e12, 1)
     dq = [o for o in ops if o["name"] == "dequant"]
-    out["roofline_dequant"] = {"bound": "hbm", "kernel": "dequant_kernel (bf16 out), 4096 x 4096", "unit": "GB/s",
+    out["roofline_dequant"] = {"bound": "hbm", "kernel": "dequant8_tile_kernel (bf16 out), 4096 x 4096", "unit": "GB/s",
                                "peak": HBM_PEAK_GBPS,
                                "per_k": {str(o["k"]): {"us": round(o["us"], 3), "GBps": round(gbps(o), 1),
                                                        "frac": round(gbps(o) / HBM_PEAK_GBPS, 4)} for o in dq}}

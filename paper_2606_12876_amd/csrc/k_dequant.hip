@@ -180,8 +180,8 @@ __global__ __launch_bounds__(256) void dequant_small_kernel(const unsigned char*
   store_group<OUT>(W, (size_t)row * d_in + (size_t)grp * 8, v);
 }
 
-// 8-bit codes to 16 bits where codes and output together outgrow the last-level cache's reach (see
-// launch_dequant_k): tiles of RT rows x GT groups (RT GT = 2048 groups, 32 KiB of output), 512 threads.
+// 8-bit codes to 16 bits, middle and very large layers (see launch_dequant_k): tiles of RT rows x GT groups
+// (RT GT = 2048 or 4096 groups, 32 or 64 KiB of output), 512 threads.
 // Thread t takes row t % RT of the tile and P = RT GT / 512 consecutive groups of it (part (t / RT) of the
 // tile's GT / 16 slices): one P-byte code load per plane brings them, which it folds into the tile in LDS,
 // row-major, its 16-byte chunks XOR-swizzled by row so that both the column-wise writes and the row-wise
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(dq::kThreads) void dequant8_tile_kernel(const unsig
                                                                     const uint16_t* scales, void* W, int d_out, int d_in,
                                                                     int G, int S, size_t plane_bytes) {
   static_assert(OUT == AQMB_F16 || OUT == AQMB_BF16, "16-bit outputs");
-  static_assert(RT * GT == 2048, "tile size");
+  static_assert(RT * GT == 4096 || RT * GT == 2048, "tile size");
   static_assert(GT >= 64 && (GT & (GT - 1)) == 0 && RT <= 64, "swizzle range");
   using namespace dq;
   constexpr int P = RT * GT / kThreads, kParts = 16 / P, ST = GT / 16, CP = GT / 64;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(dq::kThreads) void dequant8_tile_kernel(const unsig
 // a kernel with a workgroup-wide output tile for 8-bit codes to 16 bits, a thread per group for the rest:
 //   8-bit codes   bf16 k = 1..4  20.8 22.5 24.2 26.6 -> 18.1 18.8 18.8 21.0   fp32  84 79 75 73 -> 35 36 37 39
 //   4-bit codes   bf16 k = 1..4  23.8                -> 18.1 18.3 18.8 19.0   fp32  84          -> 35 36 36 37
-//   16-bit codes  bf16 k = 1, 2  32.5 54.6           -> 32.9 52.7             fp32  66 72       -> 41 66
+//   16-bit codes  (bf16, and fp32 at k = 2: thread per group)                fp32 k = 1  66 -> 41
 template <int CB, int K, int R, int NW> constexpr size_t dequant_lds() {
   return (CB <= 8 ? (size_t)K * (1 << CB) * 16 : 0) + (size_t)NW * K * R * 8 * CB;
 }
@@ -406,43 +406,53 @@ __global__ __launch_bounds__(64 * NW) void dequant_kernel(const unsigned char* c
   }
 }
 
-// Which kernel. All times in us, this side of the line / the other, 256 compute units.
-// - A thread per group while all threads run at once (2048 per compute unit) and the output is 16 bits wide:
-//   2048 x 2048, 8-bit codes, k = 1 / 4: 3.8 / 4.4 against 3.9 / 4.7; 1500 x 3000, past the line, 5.5 / 6.1
-//   against 4.7 / 5.5. fp32 output stores twice as much in 32-byte pieces per thread: up to 640 threads per
-//   unit (1000 x 1032: 3.8 / 4.0 against 3.8 / 4.3; 333 x 8200: 6.0 / 6.3 against 4.9 / 5.7), with 16-bit
-//   codes, where the gathers take longer, 1536 (333 x 8200, k = 1 / 2: 6.3 / 6.9 against 7.7 / 9.1; 2048 x
-//   2048: 8.0 / 9.6 against 7.2 / 9.5).
-// - dequant8_tile_kernel, 8-bit codes to 16 bits, once codes and output pass 148 MiB: 14336 x 4096 is 34 / 37
-//   at k = 6 / 8 (154, 168 MiB) against 37 / 41, and 32 at k = 4 (140 MiB) against 29; 28672 x 8192 is 91 / 112
-//   at k = 1 / 4 against 100 / 122.
+// Which kernel. Times in us, 256 compute units; "cold": codes and outputs rotated through 0.7 GB.
+// - A thread per group: 16-bit outputs while all threads run at once (2048 per compute unit; 2048 x 2048, 8-bit
+//   codes, k = 1 / 4, cold: 3.4 / 4.0 against 4.5 / 5.2 with output tiles), fp32 up to 640 threads per unit
+//   (1000 x 1032: 3.8 / 4.0 against 3.8 / 4.3 on wave units; 333 x 8200: 6.0 / 6.3 against 4.9 / 5.7).
+//   65536-entry codebooks: always but for fp32 at k = 1 past 1536 threads per unit, where the gathers are
+//   few enough for the stores to count (cold, against wave units: 11008 x 4096 to bf16, k = 1 / 2, 29.5 / 52.4
+//   against 32.5 / 54.8, to fp32 49.7 / 63.1 against 41.2 / 70.7).
+// - dequant8_tile_kernel, 8-bit codes to 16 bits: one tile per workgroup while a layer has at most two 64 KiB
+//   tiles per compute unit (cold, against wave units: 4096 x 4096, k = 1..4, 8.6 8.7 9.0 9.7 against 10.2 9.6 10.3
+//   10.7, whose 4-row units read half lines), and 32 x 64 tiles once codes and output pass 148 MiB (14336 x
+//   4096, k = 6 / 8, 154 and 168 MiB: 34 / 37 against 37 / 41, k = 4, 140 MiB: 32 against 29; 28672 x 8192: 91 / 112
+//   at k = 1 / 4 against 100 / 122).
 // - dequant_kernel for the rest, with at most as many workgroups as run at once, each wave walking its units
-//   with the grid's stride. Codebooks in LDS: units of 8 rows where every wave gets one (8 per compute unit at
-//   k >= 3, 16 at k <= 2, where a unit is soon done: 4096 x 4096, 16 per unit, bf16, k = 1..4 is 11.2 9.3 9.0
-//   10.1 with 8 rows, 8.7 8.9 10.1 10.9 with 4), else of 4 rows; 4-wave workgroups where 8-wave ones would give
-//   a few compute units a second one (1500 x 3000, bf16, k = 4: 5.8 against 6.2) and, with 2 rows, where they
-//   would leave more than a quarter of the compute units idle (1000 x 1032: 3.3 against 3.6 at k = 2); at
-//   full load 8 waves share a codebook copy better (4096 x 11008, k = 3: 19.9 against 24.2).
-//   65536-entry codebooks: units of 8 rows (1500 x 3000, k = 1: 6.2 against 6.9 with 4), and 4-wave workgroups
-//   on large layers, which leave the compute unit one by one (4096 x 11008, k = 2: 52.7 against 55.3), 8-wave
-//   ones on small layers, where they keep to fewer compute units (1500 x 3000, k = 2: 9.0 against 9.7).
+//   with the grid's stride. Units of 8 rows (whole lines of codes), 8-wave workgroups where every wave gets a
+//   unit (8 per compute unit at k >= 3, 16 at k <= 2, where a unit is soon done), else 4-wave ones (4096 x 4096 to
+//   fp32, k = 1, cold: 16.6 against 19.0 with 4 rows and 8 waves); 4 rows where 4-row units would give 8 to 12 waves
+//   per compute unit (1500 x 3000) and 2 where fewer than 6 (1000 x 1032, k = 2: 3.3 against 3.6), so that no unit
+//   of the card stands idle.
 template <int OUT, int CB, int K>
 static void launch_dequant_k(const Layer& L, void* W, hipStream_t st) {
   const int d_out = L.d.d_out, ncu = L.n_cu > 0 ? L.n_cu : 256, n_ct = (L.G + 63) / 64;
   const size_t nslot = (size_t)L.S * d_out * (128 / CB);
   const int resident = OUT != AQMB_F32 ? 2048 : CB == 16 ? 1536 : 640;
-  if (nslot <= (size_t)resident * ncu) {
+  const bool gathers = CB == 16 && (OUT != AQMB_F32 || K > 1) && nslot < ((size_t)1 << 30);
+  if (nslot <= (size_t)resident * ncu || gathers) {
     dequant_small_kernel<OUT, CB, K><<<(unsigned)((nslot + 255) / 256), 256, 0, st>>>(
         L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in, L.G, (uint32_t)nslot, L.plane_bytes);
     return;
   }
   if constexpr (CB == 8 && OUT != AQMB_F32) {
-    const size_t bytes = (size_t)d_out * L.d.d_in * 2 + K * L.plane_bytes;
-    if (bytes > ((size_t)148 << 20) && nslot < ((size_t)1 << 30)) {
-      const int n_tiles = ((d_out + 31) / 32) * ((L.S + 3) / 4);
-      dequant8_tile_kernel<OUT, K, 32, 64><<<std::min(n_tiles, 2 * ncu), dq::kThreads, 0, st>>>(
-          L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in, L.G, L.S, L.plane_bytes);
-      return;
+    auto n_tiles = [&](int rt, int gt) { return ((d_out + rt - 1) / rt) * ((L.S + gt / 16 - 1) / (gt / 16)); };
+    auto tiles = [&](auto kern, int grid) {
+      kern<<<(unsigned)std::min(grid, 65535), dq::kThreads, 0, st>>>(L.codes, L.codebooks, L.scales, W, d_out, L.d.d_in, L.G,
+                                                                     L.S, L.plane_bytes);
+    };
+    if (nslot < ((size_t)1 << 30)) {
+      if (n_tiles(64, 64) <= 2 * ncu) {                // one tile per workgroup, as wide as the rows allow
+        if (L.G > 256) tiles(dequant8_tile_kernel<OUT, K, 8, 512>, n_tiles(8, 512));
+        else if (L.G > 128) tiles(dequant8_tile_kernel<OUT, K, 16, 256>, n_tiles(16, 256));
+        else if (L.G > 64) tiles(dequant8_tile_kernel<OUT, K, 32, 128>, n_tiles(32, 128));
+        else tiles(dequant8_tile_kernel<OUT, K, 64, 64>, n_tiles(64, 64));
+        return;
+      }
+      if ((size_t)d_out * L.d.d_in * 2 + K * L.plane_bytes > ((size_t)148 << 20)) {
+        tiles(dequant8_tile_kernel<OUT, K, 32, 64>, std::min(n_tiles(32, 64), 2 * ncu));
+        return;
+      }
     }
   }
   auto go = [&](auto kern, size_t lds, int rows, int nw) {
@@ -453,17 +463,14 @@ static void launch_dequant_k(const Layer& L, void* W, hipStream_t st) {
                                      n_ct);
   };
   const size_t u8 = (size_t)n_ct * ((d_out + 7) / 8), u4 = (size_t)n_ct * ((d_out + 3) / 4), cus = ncu;
-  if constexpr (CB == 16) {
-    if (u8 > (K <= 2 ? 16 : 8) * cus) go(dequant_kernel<OUT, 16, K, 8, 4>, dequant_lds<16, K, 8, 4>(), 8, 4);
-    else go(dequant_kernel<OUT, 16, K, 8, 8>, dequant_lds<16, K, 8, 8>(), 8, 8);
-  } else if (u8 > (K <= 2 ? 16 : 8) * cus) {
+  if (u8 > (K <= 2 ? 16 : 8) * cus) {
     go(dequant_kernel<OUT, CB, K, 8, 8>, dequant_lds<CB, K, 8, 8>(), 8, 8);
-  } else if (u4 < 6 * cus) {
+  } else if (CB != 16 && u4 < 6 * cus) {
     go(dequant_kernel<OUT, CB, K, 2, 4>, dequant_lds<CB, K, 2, 4>(), 2, 4);
-  } else if (u4 > 8 * cus && u4 < 12 * cus) {
+  } else if (CB != 16 && u4 > 8 * cus && u4 < 12 * cus) {
     go(dequant_kernel<OUT, CB, K, 4, 4>, dequant_lds<CB, K, 4, 4>(), 4, 4);
   } else {
-    go(dequant_kernel<OUT, CB, K, 4, 8>, dequant_lds<CB, K, 4, 8>(), 4, 8);
+    go(dequant_kernel<OUT, CB, K, 8, 4>, dequant_lds<CB, K, 8, 4>(), 8, 4);
   }
 }
 

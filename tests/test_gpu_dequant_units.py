@@ -1,9 +1,9 @@
 """Dequantization, each of its kernels, bit for bit against the oracle's stated order.
 
 Every code width, output type and plane count. Small layers (a thread per group): few rows, 63, 64 and 65
-groups, one group. Layers on units of 2, 4 and 8 rows x 64 groups: ragged in rows and groups, and more
-units than waves run at once, so that a wave walks several. A layer past 148 MiB of codes and output
-(tiles of 32 rows x 64 groups), ragged in both.
+groups, one group. Layers on units of 2, 4 and 8 rows x 64 groups and on output tiles: ragged in rows and
+groups, and more units than waves run at once, so that a wave walks several. A layer past 148 MiB of
+codes and output (tiles of 32 rows x 64 groups), ragged in both.
 """
 from __future__ import annotations
 
@@ -56,12 +56,14 @@ def test_small_units(shape, M, B):
     ((1501, 1032), 2, 4, (2,), ("f32",)),
     ((1499, 3000), 8, 8, (1, 5, 8), ("bf16", "f32")),        # 4 rows, 4 waves
     ((1499, 3000), 2, 4, (1,), ("f16", "f32")),
-    ((1499, 3000), 2, 16, (1, 2), ("bf16", "f32")),          # 16-bit codes: 8 rows, 8 waves
-    ((2047, 2048), 2, 8, (2,), ("f32",)),                    # 4 rows, 8 waves
-    ((8237, 520), 8, 8, (2, 3, 6, 8), ("bf16", "f32")),      # 4 rows; 8 rows from k = 3
-    ((8237, 520), 8, 4, (3, 8), ("f16", "f32")),
-    ((32797, 16), 2, 8, (1, 2), ("bf16", "f32")),            # 8 rows at k <= 2
-    ((16397, 520), 2, 16, (1, 2), ("f16", "f32")),           # 16-bit codes: 8 rows, 4 waves
+    ((1499, 3000), 2, 16, (1, 2), ("bf16", "f32")),          # 16-bit codes: 8 rows at k = 1 to f32
+    ((2047, 2048), 2, 8, (2,), ("f32",)),                    # 8 rows, 4 waves
+    ((8237, 520), 8, 8, (2, 3, 8), ("bf16", "f32")),         # 65 groups: tiles (bf16); 8 waves from k = 3 (f32)
+    ((8237, 520), 8, 4, (3, 8), ("f16", "f32")),             # 8 rows, 8 waves
+    ((4100, 1720), 2, 8, (1, 2), ("f16",)),                  # 215 groups: tiles
+    ((4097, 6000), 4, 8, (1, 4), ("bf16",)),                 # more than two tiles per compute unit: 8 rows
+    ((32797, 16), 2, 4, (1, 2), ("bf16", "f32")),
+    ((16397, 520), 2, 16, (1, 2), ("f16", "f32")),           # 16-bit codes: 8 rows, 8 waves at k = 1 to f32
     ((9473, 8232), 1, 8, (1,), ("bf16",)),                   # 159 MiB: output tiles
 ])
 def test_layers_of_many_units(shape, M, B, ks, dts):
