@@ -427,7 +427,7 @@ static aqmb_status gemm_impl(aqmb_layer_t layer, int k, const void* X, int n_tok
   const bool small = tiling == AQMB_GEMM_ROWS16 || (tiling == AQMB_GEMM_AUTO && n_tokens <= kGemmSmallMax);
   const int tile = tiling == AQMB_GEMM_256x128 ? 0 : tiling == AQMB_GEMM_128x128 ? 1 : tiling == AQMB_GEMM_128x64 ? 2 : -1;
   if (tiling == AQMB_GEMM_AUTO && gemm_takes_mid(*L, k, n_tokens)) {
-    const hipError_t em = launch_gemm_mid(*L, k, X, n_tokens, Y, y_dtype, (hipStream_t)stream);
+    const hipError_t em = launch_gemm_mid(*L, k, X, n_tokens, Y, y_dtype, 0, 0, (hipStream_t)stream);
     return em == hipSuccess ? AQMB_OK : hip_fail(em, where);
   }
   hipError_t e = small ? launch_gemm_small(*L, k, X, n_tokens, Y, y_dtype, (hipStream_t)stream)
@@ -445,6 +445,29 @@ aqmb_status aqmb_gemm_select(aqmb_layer_t layer, int k, const void* X, int n_tok
                              aqmb_gemm_tiling tiling, aqmb_stream_t stream) {
   clear_error();
   return gemm_impl(layer, k, X, n_tokens, Y, y_dtype, tiling, stream, "gemm_select");
+}
+
+// Not part of the interface (absent from aqmb.h), for the tests: the split-input GEMM with a tile shape of
+// 16 rb weight rows x 16 nb_max tokens, whatever the rule would choose.
+aqmb_status aqmb_test_gemm_mid(aqmb_layer_t layer, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, int rb,
+                               int nb_max, aqmb_stream_t stream) {
+  clear_error();
+  Layer* L = (Layer*)layer;
+  if (!is_live(L)) return fail(AQMB_EINVAL, "test_gemm_mid: not a live layer");
+  aqmb_status s = validate_call(&L->d, 1, k, n_tokens, AQMB_BF16, y_dtype, X, Y);
+  if (s != AQMB_OK) return s;
+  if (gemm_mid_us(*L, k, n_tokens) < 0) return fail(AQMB_EUNSUPPORTED, "test_gemm_mid: not served");
+  if ((s = check_resident(L, k, "test_gemm_mid")) != AQMB_OK || (s = check_device(L)) != AQMB_OK) return s;
+  const hipError_t e = launch_gemm_mid(*L, k, X, n_tokens, Y, y_dtype, rb, nb_max, (hipStream_t)stream);
+  return e == hipSuccess ? AQMB_OK : e == hipErrorInvalidValue ? fail(AQMB_EINVAL, "test_gemm_mid: no such tile") : hip_fail(e, "test_gemm_mid");
+}
+
+// For the tests: the byte offset from a token tile's first token (t0 of n, tiles of 16 nb tokens) at which the
+// split-input GEMM reads piece `piece` of the tile's row `row`, rows of d_in inputs.
+uint32_t aqmb_test_gemm_mid_offset(int n, int t0, int nb, int d_in, int row, int piece) {
+  const uint32_t row_b = (uint32_t)d_in * 2, last = gemm_mid_x_offset(gemm_mid_last_row(n, t0, nb), row_b, piece);
+  const uint32_t off = gemm_mid_x_offset(row, row_b, piece);
+  return off < last ? off : last;
 }
 
 aqmb_status aqmb_gemm_workspace_bytes(aqmb_layer_t layer, int k, int n_tokens, size_t* bytes) {

@@ -123,15 +123,15 @@ __global__ __launch_bounds__(64 * (RB * NB <= 16 ? 16 : 8)) void gemm_mid_kernel
   // x 128 bytes; the 16-byte pieces of a token are swizzled by (token / 2) % 8. The walk's position is
   // kept in three counters (units past the end repeat the last run: their loads are never read).
   int lb = 0, lslot = 0, lch = 0, li = 0;
-  const uint32_t row_b = (uint32_t)a.d_in * 2;                // bytes of a token (at most 2^21, see launch_gemm_mid)
+  const uint32_t row_b = (uint32_t)a.d_in * 2;                // bytes of a token (at most 2^21, see gemm_mid_us)
   const char* Xt = (const char*)(a.X + (size_t)t0 * a.d_in);  // the tile's first token
-  const uint32_t last_row = (uint32_t)(a.n - 1 - t0);         // tokens past the last read it again, never stored
+  const uint32_t last_row = gemm_mid_last_row(a.n, t0, nb);   // tokens past the last read it again, never stored
   uint32_t off0[2], off_max[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const uint32_t tr = h * 8 + (lane >> 3), piece = (lane & 7) ^ ((tr >> 1) & 7);
-    off0[h] = tr * row_b + piece * 16;
-    off_max[h] = last_row * row_b + piece * 16;
+    off0[h] = gemm_mid_x_offset(tr, row_b, piece);
+    off_max[h] = gemm_mid_x_offset(last_row, row_b, piece);
   }
   int lk0 = mine > 0 ? run_of(0) * 128 : 0;
   uint32_t lrow = 0;                                          // lb * 16 * row_b
@@ -312,7 +312,7 @@ static hipError_t launch_shape(Args& a, int rb, int nb_max, hipStream_t st) {
 // and 13.2 at k = 4, 32 x 32 8.9 and 14.5, 32 x 128 17.3 and 22.6, 48 x 64 13.5 and 22.1, 48 x 192 35.5 at
 // k = 4, 64 x 128 25.0 and 32.8).
 struct MidTile { int rb, nb_max, nb, n_tt; double us; };
-static MidTile mid_tile(const Layer& L, int k, int n) {
+static MidTile mid_tile(const Layer& L, int k, int n, int rb = 0, int nb_max = 0) {   // rb > 0: that shape only
   static const struct { int rb, nb; double start, plane, block; } shapes[9] = {
       {1, 2, 5.3, 0.73, 1.0}, {1, 4, 6.0, 0.73, 1.0},  {2, 2, 4.8, 0.9, 1.15},
       {2, 4, 5.6, 0.78, 1.2}, {2, 8, 5.0, 0.82, 1.4},  {3, 4, 5.2, 0.95, 1.35},
@@ -321,6 +321,7 @@ static MidTile mid_tile(const Layer& L, int k, int n) {
   const double len = L.d.d_in / 4096.0;
   MidTile best{};
   for (const auto& s : shapes) {
+    if (rb > 0 && (s.rb != rb || s.nb != nb_max)) continue;
     const int tt = (blocks + s.nb - 1) / s.nb, b = (blocks + tt - 1) / tt;
     const long long wgs = (long long)((L.d.d_out + 16 * s.rb - 1) / (16 * s.rb)) * tt;
     const double us = (double)((wgs + ncu - 1) / ncu) * (s.start + len * (s.plane * s.rb * k + s.block * b));
@@ -334,7 +335,10 @@ double gemm_mid_us(const Layer& L, int k, int n_tokens) {
   return mid_tile(L, k, n_tokens).us;
 }
 
-hipError_t launch_gemm_mid(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, hipStream_t st) {
+hipError_t launch_gemm_mid(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, int rb,
+                           int nb_max, hipStream_t st) {
+  const MidTile tile = mid_tile(L, k, n_tokens, rb, nb_max);
+  if (tile.rb == 0) return hipErrorInvalidValue;
   gmid::Args a{};
   a.codes = L.codes;
   a.codebooks = L.codebooks;
@@ -348,8 +352,8 @@ hipError_t launch_gemm_mid(const Layer& L, int k, const void* X, int n_tokens, v
   a.G = L.G;
   a.n = n_tokens;
   a.y_dtype = (int)y_dtype;
-  const MidTile tile = mid_tile(L, k, n_tokens);
-  const int rb = tile.rb, nb_max = tile.nb_max;
+  rb = tile.rb;
+  nb_max = tile.nb_max;
   a.nb = tile.nb;
   a.n_tt = tile.n_tt;
   if (L.d.code_bits == 4) switch (k) {

@@ -59,11 +59,23 @@ hipError_t launch_beam_mma(const aqmb_desc& d, int k, int beam_width, const void
 // Prefill GEMM tiled for small token counts (same arithmetic as launch_gemm).
 hipError_t launch_gemm_small(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                              hipStream_t st);
+// Addresses in a token tile of the split-input GEMM: tokens t0 .. t0 + 16 nb - 1 of n, 32-bit byte
+// offsets from the tile's first token. The tile's last row is taken before it is multiplied: n - t0 rows
+// of X may span more than 2^32 bytes, 16 nb rows of at most 2^21 bytes do not.
+__host__ __device__ inline uint32_t gemm_mid_last_row(int n, int t0, int nb) {
+  const int left = n - 1 - t0, tile = 16 * nb - 1;
+  return (uint32_t)(left < tile ? left : tile);
+}
+__host__ __device__ inline uint32_t gemm_mid_x_offset(uint32_t row, uint32_t row_bytes, uint32_t piece) {
+  return row * row_bytes + piece * 16;
+}
 // Prefill GEMM for tens to hundreds of tokens, k <= 4 (same arithmetic).
 // gemm_mid_us: its estimated time (-1 where it does not serve the call).
 double gemm_mid_us(const Layer& L, int k, int n_tokens);
-hipError_t launch_gemm_mid(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
-                           hipStream_t st);
+// rb, nb_max: weight rows / 16 and token blocks of the tile (0, 0: the rule's choice; a pair that is not
+// one of its nine shapes is hipErrorInvalidValue).
+hipError_t launch_gemm_mid(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, int rb,
+                           int nb_max, hipStream_t st);
 // Large-tile prefill GEMM; tile: -1 = chosen by the number of workgroup rounds, 0 = 256 x 128,
 // 1 = 128 x 128, 2 = 128 x 64 (tokens x weight rows).
 hipError_t launch_gemm(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, int tile,
