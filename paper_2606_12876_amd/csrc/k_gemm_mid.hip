@@ -219,6 +219,13 @@ __global__ __launch_bounds__(64 * (RB * NB <= 16 ? 16 : 8)) void gemm_mid_kernel
           }
           w[r][j] = fold<K>(cw);
         }
+      if (run * 16 + 16 > a.G) {                              // (uniform) the ragged last run: the groups past d_in are padding
+#pragma unroll                                                // of code 0; zero weights, as codeword 0 may not be finite
+        for (int j = 0; j < 2; ++j)
+          if (run * 16 + c * 8 + 2 * kc + j >= a.G)
+#pragma unroll
+            for (int r = 0; r < RB; ++r) w[r][j] = __builtin_bit_cast(b16x8_t, make_uint4(0, 0, 0, 0));
+      }
       b16x8_t x0[2], x1[2];
       wait_vmcnt<2 * (kR - 1)>();
       read_unit(x0);
