@@ -15,8 +15,9 @@
 // tuple from the roundings actually made) is then evaluated exactly and ranked by (error, tuple):
 // about 12 candidates per group instead of 2048. The bound is one-sided and rigorous, so no
 // candidate that belongs into the beam is missed. Groups the bound cannot serve (values or
-// codebooks that are not finite, a zero scale, more near-ties than the list holds) are searched by
-// the wave exhaustively, in the same order of decisions.
+// codebooks that are not finite, more near-ties than the list holds) are searched by the wave
+// exhaustively, in the same order of decisions; a zero scale or a weight that is not a number
+// decides a group at once.
 //
 // A wave owns 32 groups (plain: 32 consecutive groups of the matrix; data-aware: 32 rows of one
 // group column, which share H) from the first stage to the last: stage 0 has one tuple per group
@@ -290,66 +291,202 @@ __device__ __forceinline__ void store_row(float* row, const Tuple& t) {
 // Exhaustive search of stage m of group gl by the whole wave, with the decisions of k_beam.hip:
 // candidates in the order (error, key), unordered errors never taken, a missing entry is
 // (inf, 0xFFFFFFFF) with code 0xFF and no parent. Returns whether one was missing.
+// A lane evaluates 32 candidates as (ordered error, key, p) words, all different. The keep smallest lie
+// in the keep lanes with the smallest minima: those lanes list theirs up to the keep-th minimum, and the
+// listed words (about keep, at most 32 keep) are ranked. Bound: vector issue, two thirds of it the errors.
 template <bool WT>
 __device__ __noinline__ bool slow_group(WaveMem& M, const Tables& tb, int m, int gl, int n_par, int keep, bool last) {
   const int lane = threadIdx.x & 63;
   const float ginv = pow2f(-tb.info[m].g), s = M.s[gl], ns2 = -s * ginv;
+  const uint4* bk = tb.books + m * 256;
+  const float* Q = tb.Q + m * 256;
+  wave_sync();                                      // the list and the rows are free
   if (lane < n_par) store_row(M.rs[lane], load_tuple<WT>(M, tb, m, gl, lane));
+  if (lane == 0) M.cnt[0][0] = 0;
   wave_sync();
-  float e[32];
+  unsigned long long y[32], lm = ~0ull;
 #pragma unroll
-  for (int n = 0; n < 32; ++n) {
-    e[n] = __builtin_nanf("");
-    if ((n >> 2) < n_par) {
-      const int c = (n & 3) * 64 + lane;
+  for (int p = 0; p < 8; ++p) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[4 * p + i] = ~0ull;
+    if (p < n_par) {                                // (uniform)
       float v[8];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) v[t] = M.rs[n >> 2][t];
-      e[n] = exact_error<WT>(v, M.rs[n >> 2][8], tb.books[m * 256 + c], s, ns2, ginv, WT ? tb.Q[m * 256 + c] : 0.f);
+      for (int t = 0; t < 8; ++t) v[t] = M.rs[p][t];
+      const uint32_t low = (ubits(M.rs[p][9]) << 16) | (uint32_t)(lane << 8) | (uint32_t)p;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float e = exact_error<WT>(v, M.rs[p][8], bk[i * 64 + lane], s, ns2, ginv, WT ? Q[i * 64 + lane] : 0.f);
+        y[4 * p + i] = e == e ? ((unsigned long long)ordered(e) << 32) | (low + (uint32_t)(i << 14)) : ~0ull;
+        lm = y[4 * p + i] < lm ? y[4 * p + i] : lm;
+      }
     }
   }
-  if (lane < 8 && lane >= keep) M.ky[gl][lane] = 0xFFFFu;
-  bool missing = false;
-  for (int q = 0; q < keep; ++q) {
-    float be = __builtin_inff();
-    uint32_t bkey = 0xFFFFFFFFu, bid = 0xFFFFFFFFu;
+  M.list[lane] = lm;
+  wave_sync();
+  int at = 0;                                       // rank of the lane's minimum
+#pragma unroll 8
+  for (int i = 0; i < 64; ++i) at += M.list[i] < lm ? 1 : 0;
+  const unsigned long long kth = __ballot(at == keep - 1 && lm != ~0ull);   // none: all that are ordered
+  const int src = kth ? __builtin_ctzll(kth) : 0;
+  unsigned long long T = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(lm >> 32), src) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)lm, src);
+  if (!kth) T = ~0ull - 1;
+  unsigned long long* list = M.list + 64;           // at most 32 keep <= 256 entries
+  if (lm <= T) {
+    uint32_t n = 0;
 #pragma unroll
-    for (int n = 0; n < 32; ++n) {
-      const uint32_t key = (ubits(M.rs[n >> 2][9]) << 8) | (uint32_t)((n & 3) * 64 + lane);
-      const bool bt = before(e[n], key, be, bkey);
-      be = bt ? e[n] : be;
-      bkey = bt ? key : bkey;
-      bid = bt ? (uint32_t)(n * 64 + lane) : bid;
-    }
+    for (int i = 0; i < 32; ++i) n += y[i] <= T ? 1u : 0u;
+    uint32_t pos = atomicAdd(&M.cnt[0][0], n);
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      const float oe = __shfl_xor(be, o, 64);
-      const uint32_t ok = __shfl_xor(bkey, o, 64), oi = __shfl_xor(bid, o, 64);
-      const bool bt = before(oe, ok, be, bkey) || (oe == be && ok == bkey && oi < bid);
-      be = bt ? oe : be;
-      bkey = bt ? ok : bkey;
-      bid = bt ? oi : bid;
-    }
-#pragma unroll
-    for (int n = 0; n < 32; ++n)
-      if (bid == (uint32_t)(n * 64 + lane)) e[n] = __builtin_nanf("");
-    uint2 codes = make_uint2(0u, 0u);
-    if (bkey != 0xFFFFFFFFu) {
-      const float* row = M.rs[(bid >> 8) & 7];
-      codes = make_uint2(ubits(row[10]), ubits(row[11]));
-    } else {
-      missing = true;
-    }
-    const uint32_t c = bkey & 0xFFu;
-    if (m < 4) codes.x |= c << (8 * m); else codes.y |= c << (8 * (m - 4));
-    if (lane == 0) {
-      M.st[gl][q] = codes;
-      M.ky[gl][q] = (uint16_t)bkey;
-      if (last) M.oute[gl] = be;
+    for (int i = 0; i < 32; ++i)
+      if (y[i] <= T) list[pos++] = y[i];
+  }
+  wave_sync();
+  const int total = __builtin_amdgcn_readfirstlane((int)M.cnt[0][0]);
+  if (lane < ((-total) & 7)) list[total + lane] = ~0ull;
+  if (lane < 8 && lane >= min(total, keep)) {       // missing entries; none kept from `keep` on
+    M.ky[gl][lane] = 0xFFFFu;
+    if (lane < keep) {
+      M.st[gl][lane] = make_uint2(m < 4 ? 0xFFu << (8 * m) : 0u, m < 4 ? 0u : 0xFFu << (8 * (m - 4)));
+      if (last) M.oute[gl] = __builtin_inff();
     }
   }
   wave_sync();
-  return missing;
+  for (int q = lane; q < total; q += 64) {
+    const unsigned long long z = list[q];
+    int r = 0;
+    for (int i = 0; i < total; i += 8) {
+#pragma unroll
+      for (int h = 0; h < 8; ++h) r += list[i + h] < z ? 1 : 0;
+    }
+    if (r < keep) {
+      const uint32_t lo = (uint32_t)z, key = lo >> 8, c = key & 0xFFu;
+      const float* row = M.rs[lo & 0xFFu];
+      uint2 nc = make_uint2(ubits(row[10]), ubits(row[11]));
+      if (m < 4) nc.x |= c << (8 * m); else nc.y |= c << (8 * (m - 4));
+      M.st[gl][r] = nc;
+      M.ky[gl][r] = (uint16_t)key;
+      if (last) {                                   // again, for the sign of a zero
+        float v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = row[t];
+        M.oute[gl] = exact_error<WT>(v, row[8], bk[c], s, ns2, ginv, WT ? Q[c] : 0.f);
+      }
+    }
+  }
+  wave_sync();
+  return total < keep;
+}
+
+// y into the ascending list, dropping its last entry.
+template <int N> __device__ __forceinline__ void insert(unsigned long long (&l)[N], unsigned long long y) {
+  bool lt[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) lt[q] = y < l[q];
+#pragma unroll
+  for (int q = N - 1; q > 0; --q) l[q] = lt[q] ? (lt[q - 1] ? l[q - 1] : y) : l[q];
+  l[0] = lt[0] ? y : l[0];
+}
+
+// The same exhaustive search for all groups in `left` at once, two lanes per group (even and odd codewords),
+// each with a sorted list of (ordered error, key, p) words; the lists are joined at the end. Returns the
+// groups with a missing entry. Per group this costs the errors and the insertions, but always for 32 groups;
+// slow_group costs about 1000 instructions of its own per group. 2048 x 2048, k = 4, beams 8 / 5 / 2, us, all
+// groups left: one NaN in every codebook 18950 / 13050 / 6750 with a wave per group (every minimum by its own
+// wave-wide search) -> 4480 / 3320 / 1090, all codewords equal 19100 / 13150 / 6770 -> 4130 / 2980 / 1340, a
+// last codebook of zeros at beam 8 2620 -> 1510. The lane-per-group search of k_beam.hip, 8 waves per SIMD
+// against 2 here, takes 3020 / 1470 / 510, 1820 / 1070 / 455 and 2990 on these: inputs that tell no codes
+// apart do not pay for a second kernel.
+template <bool WT, int PC>
+__device__ __noinline__ uint32_t slow_unit(WaveMem& M, const Tables& tb, int m, uint32_t left, int n_par, int keep, bool last) {
+  const int lane = threadIdx.x & 63, gl = lane & 31, half = lane >> 5;
+  const float ginv = pow2f(-tb.info[m].g), s = M.s[gl], ns2 = -s * ginv, inf = __builtin_inff();
+  constexpr unsigned long long kNone = 0xFF800000FFFFFFFFull;   // (inf, no key)
+  float v[PC][8], base[PC], best = inf;
+  uint32_t low[PC];                                 // rank, p of the keys
+  unsigned long long l[PC];
+  wave_sync();
+#pragma unroll
+  for (int p = 0; p < PC; ++p) {
+    low[p] = 0;
+    base[p] = 0.f;
+    l[p] = kNone;
+    if (p < n_par) {                                // (uniform)
+      const Tuple t = load_tuple<WT>(M, tb, m, gl, p);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[p][i] = t.v[i];
+      base[p] = t.base;
+      low[p] = (t.rank << 16) | (uint32_t)p;
+    }
+  }
+  float thr = inf;                                  // no smaller than the keep-th smallest error of the group
+  for (int c0 = half; c0 < 256; c0 += 8) {          // four codewords at a time: four chains of sums in flight
+    uint4 C[4];
+    float q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      C[i] = tb.books[m * 256 + c0 + 2 * i];
+      q[i] = WT ? tb.Q[m * 256 + c0 + 2 * i] : 0.f;
+    }
+#pragma unroll
+    for (int p = 0; p < PC; ++p)
+      if (p < n_par) {
+        float e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = exact_error<WT>(v[p], base[p], C[i], s, ns2, ginv, q[i]);
+        const float em = __builtin_fminf(__builtin_fminf(e[0], e[1]), __builtin_fminf(e[2], e[3]));
+        if (em <= thr) {
+          const uint32_t key0 = low[p] + (uint32_t)(c0 << 8);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const uint32_t key = key0 + (uint32_t)(i << 9);
+            if (last) {
+              const uint32_t at = (uint32_t)l[0];
+              const bool bt = before(e[i], key, best, at);
+              best = bt ? e[i] : best;
+              l[0] = bt ? key : at;
+            } else if (e[i] <= thr) {
+              const unsigned long long y = ((unsigned long long)ordered(e[i]) << 32) | key;
+              if (y < l[PC - 1]) insert<PC>(l, y);
+            }
+          }
+        }
+      }
+    // Each half has (PC + 1) / 2 errors up to its own bound.
+    const Halves h = halves(last ? best : unordered((uint32_t)(l[(PC - 1) / 2] >> 32)));
+    thr = last || PC == 1 ? min2(h.a, h.b) : max2(h.a, h.b);
+  }
+  if (last) l[0] = ((unsigned long long)ordered(best) << 32) | (uint32_t)l[0];
+  unsigned long long o[PC];
+#pragma unroll
+  for (int q = 0; q < PC; ++q) o[q] = __shfl_xor(l[q], 32, 64);
+  const float ob = __shfl_xor(best, 32, 64);
+  best = o[0] < l[0] ? ob : best;                   // with the sign of a zero
+#pragma unroll
+  for (int q = 0; q < PC; ++q) insert<PC>(l, o[q]);
+  bool missing = false;
+  uint2 codes[PC];
+#pragma unroll
+  for (int q = 0; q < PC; ++q) {
+    const uint32_t key = (uint32_t)l[q], c = (key >> 8) & 0xFFu;
+    const bool none = key == 0xFFFFFFFFu;           // code 255, no parent
+    missing = missing || (none && q < keep);
+    codes[q] = make_uint2(0u, 0u);
+    if (m > 0 && !none) codes[q] = M.st[gl][key & 7u];
+    if (m < 4) codes[q].x |= c << (8 * m); else codes[q].y |= c << (8 * (m - 4));
+  }
+  wave_sync();                                      // every read of the tuples is done
+  if (half == 0 && ((left >> gl) & 1u)) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (q < PC && q < keep) M.st[gl][q] = codes[q < PC ? q : 0];
+      M.ky[gl][q] = q < PC && q < keep ? (uint16_t)((uint32_t)l[q < PC ? q : 0] >> 8) : (uint16_t)0xFFFFu;
+    }
+    if (last) M.oute[gl] = best;
+  }
+  wave_sync();
+  return left & (uint32_t)__ballot(missing);
 }
 
 // Stage m of the wave's 32 groups, n_par <= PC kept tuples each: the keep best candidates replace
@@ -696,14 +833,53 @@ __global__ __launch_bounds__(64 * kWaves) void beam_mma_kernel(Args a) {
       M.s[lane] = f16_to_f32(a.scales[row]);
     }
     wave_sync();
-    uint32_t taint = 0;
-    for (int m = 0; m < a.k; ++m) {
+    // Groups that the filter cannot serve: a zero scale, weights or a scale that are not finite. With a zero
+    // scale and all else finite every candidate has the error of code 0, which comes first; with a weight that
+    // is not a number no candidate has one, and every stage's entries are missing.
+    uint32_t taint = 0, done, hopeless;
+    {
+      const Tuple t = load_tuple<WT>(M, tb, 0, lane & 31, 0);
+      const uint4 w = M.w[lane & 31];
+      const float s = M.s[lane & 31];
+      const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+      bool nan = false, inf = false, zero = s == 0.f && fabsf(t.base) < 1e30f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t lo = u[q] & 0x7FFFu, hi = (u[q] >> 16) & 0x7FFFu;
+        nan = nan || lo > 0x7C00u || hi > 0x7C00u;
+        inf = inf || lo == 0x7C00u || hi == 0x7C00u;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) zero = zero && fabsf(t.v[i]) < 1e30f;
+      for (int m = 0; m < a.k; ++m) zero = zero && !info[m].bad;
+      zero = zero && !inf && !nan;
+      hopeless = (uint32_t)__ballot(nan || inf || s == 0.f || !(fabsf(s) < 1e30f));
+      done = (uint32_t)__ballot(zero || nan);
+      if (lane < 32 && (zero || nan)) {
+        const int m = a.k - 1;
+        const float ginv = pow2f(-info[m].g);
+        const uint32_t c = nan ? 0xFFu : 0u;
+        M.st[lane][0] = make_uint2(m < 4 ? c << (8 * m) : 0u, m < 4 ? 0u : c << (8 * (m - 4)));
+        M.oute[lane] = nan ? __builtin_inff()
+                           : exact_error<WT>(t.v, t.base, books[m * 256], s, -s * ginv, ginv, WT ? Qs[m * 256] : 0.f);
+      }
+      wave_sync();
+    }
+    for (int m = 0; m < a.k && done != ~0u; ++m) {
       const bool last = m == a.k - 1;
       const int n_par = m == 0 ? 1 : a.beam, keep = last ? 1 : a.beam;
-      uint32_t left = m == 0 ? beam_stage<WT, 1>(M, tb, m, n_par, keep, last, taint)
-                             : beam_stage<WT, PCB>(M, tb, m, n_par, keep, last, taint);
-      if (last) left = last_stage<WT>(M, tb, m, left);
-      left = __builtin_amdgcn_readfirstlane(left);
+      uint32_t left = ~0u;
+      if (!info[m].bad && (taint | hopeless) != ~0u) {   // else the filter serves none of them
+        left = m == 0 ? beam_stage<WT, 1>(M, tb, m, n_par, keep, last, taint)
+                      : beam_stage<WT, PCB>(M, tb, m, n_par, keep, last, taint);
+        if (last) left = last_stage<WT>(M, tb, m, left);
+      }
+      left = __builtin_amdgcn_readfirstlane(left & ~done);
+      // slow_unit: 32 candidates per tuple and group of about 28 instructions; slow_group: 1000 and 4 per tuple
+      if (__builtin_popcount(left) >= 2 + 3 * n_par) {
+        taint |= slow_unit<WT, PCB>(M, tb, m, left, n_par, keep, last);
+        left = 0;
+      }
       while (left) {
         const int gl = __builtin_ctz(left);
         left &= left - 1;
