@@ -92,7 +92,7 @@ __global__ __launch_bounds__(64 * (CW + 4)) void gemm_kernel(const unsigned char
                                                               const uint16_t* __restrict__ scales,
                                                               const uint16_t* __restrict__ X, void* __restrict__ Y,
                                                               int n_tokens, int d_out, int d_in, int G,
-                                                              size_t plane_bytes, int n_tb, int n_cb, int stagger) {
+                                                              size_t plane_bytes, int n_tb, int n_cb) {
   using namespace gemm;
   constexpr int kDepth = x_depth<K>();
   constexpr int NCW = 1 << CB;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64 * (CW + 4)) void gemm_kernel(const unsigned char
   const int tb = blockIdx.x % n_tb, cb = blockIdx.x / n_tb;
   const int n0 = tb * BMT, i0 = cb * BNT;
   const int nsteps = (d_in + BK - 1) / BK;
-  const int s0 = stagger ? (int)(((long long)cb * nsteps) / n_cb) : 0;
+  const int s0 = (int)(((long long)cb * nsteps) / n_cb);
   auto step_of = [&](int seq) { int st = s0 + seq; return st >= nsteps ? st - nsteps : st; };
 
   for (int q = tid; q < K * NCW; q += kThreads) cbs[q] = ((const uint4*)codebooks)[q];
@@ -591,18 +591,21 @@ static bool gemm_dense256(const Layer& L, int n_tokens) {
 template <int K, int CB, int BMT, int BNT, int CW>
 static void launch_kcm(const Layer& L, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype, hipStream_t st) {
   using namespace gemm;
-  const int stagger = !gemm_dense256(L, n_tokens);
   constexpr int kDepth = x_depth<K>();
   const int n_tb = (n_tokens + BMT - 1) / BMT, n_cb = (L.d.d_out + BNT - 1) / BNT;
+  // The kernel starts column block cb at step cb nsteps / n_blocks: 2^30 gives step 0 for all of them (cb nsteps
+  // is below 2^24). An argument of its own for this cost every call scalar registers (8-bit codes, k = 1:
+  // 1133 x 2600, 3165 tokens 40.7 -> 43.4 us; 1554 x 2384, 2099 tokens 38.2 -> 40.0; k = 4 1-2 %).
+  const int n_blocks = gemm_dense256(L, n_tokens) ? 1 << 30 : n_cb;
   const size_t lds = ((size_t)kDepth * x_stage<BMT>() + 2 * slab_elems<BNT>()) * 2 + (size_t)K * (1 << CB) * 16 +
                      (size_t)kCodeDepth * 4 * K * 64 * 4;
   const dim3 grid(n_tb * n_cb);
   if (y_dtype == AQMB_BF16)
     gemm_kernel<K, AQMB_BF16, CB, BMT, BNT, CW><<<grid, 64 * (CW + 4), lds, st>>>(
-        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_cb, stagger);
+        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_blocks);
   else
     gemm_kernel<K, AQMB_F32, CB, BMT, BNT, CW><<<grid, 64 * (CW + 4), lds, st>>>(
-        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_cb, stagger);
+        L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_blocks);
 }
 
 // One round of 256 workgroups measured on a 4096-input layer (k = 1..4, us), the part above 5 us in
