@@ -608,14 +608,20 @@ static void launch_kcm(const Layer& L, const void* X, int n_tokens, void* Y, aqm
         L.codes, L.codebooks, L.scales, (const uint16_t*)X, Y, n_tokens, L.d.d_out, L.d.d_in, L.G, L.plane_bytes, n_tb, n_blocks);
 }
 
-// One round of 256 workgroups measured on a 4096-input layer (k = 1..4, us), the part above 5 us in
-// proportion to d_in; a last round that is not full counts 0.7 (11008 x 4096, 900 tokens, 1.34 rounds
-// of 256 x 128: 165 us at k = 4, 128 us at k = 1).
+// Per round of workgroups (a started round counts whole: a round of one workgroup takes as long): a start and,
+// for 4096 inputs, the times below (8- and 4-bit codes, k = 1..4, us). Two workgroups of the 128 x 64 tiling
+// fit a compute unit while few codebooks are held: two rounds take 1.6. Fitted to 2500 layers and token counts
+// (as k_gemm_mid.hip's): measured at 0.9 to 1.15 of the estimate, 256 x 128 tiles up to 1.2.
 double gemm_large_us(const Layer& L, int k, int n_tokens) {
-  static const double us[3][4] = {{72.0, 77.5, 86.6, 96.8}, {52.0, 60.0, 68.0, 77.0}, {36.0, 41.0, 47.0, 53.0}};
-  const int bm[3] = {256, 128, 128}, bn[3] = {128, 128, 64};
+  static const double us[3][2][4] = {{{54.5, 60.5, 65.5, 74.0}, {54.0, 57.5, 60.0, 64.0}},
+                                     {{46.5, 52.5, 60.5, 67.5}, {43.0, 46.5, 53.5, 60.0}},
+                                     {{29.5, 34.5, 40.5, 45.5}, {28.5, 32.0, 36.5, 39.5}}};
+  const int bm[3] = {256, 128, 128}, bn[3] = {128, 128, 64}, bits4 = L.d.code_bits == 4;
+  const long long ncu = L.n_cu > 0 ? L.n_cu : 256;
   const int c = gemm_tile(L, n_tokens, -1);
-  return gemm_rounds(L, n_tokens, bm[c], bn[c]) * (5.0 + (us[c][k - 1] - 5.0) * L.d.d_in / 4096.0);
+  const long long wg = (long long)((n_tokens + bm[c] - 1) / bm[c]) * ((L.d.d_out + bn[c] - 1) / bn[c]), r = (wg + ncu - 1) / ncu;
+  const double rounds = c == 2 && k <= 2 + bits4 ? 1.6 * (r / 2) + (r == 1 ? 1.0 : r % 2 ? 0.75 : 0.0) : (double)r;
+  return rounds * ((c == 0 ? (k <= 2 ? 6.7 : 9.8) : c == 1 ? 6.3 : 5.0) + us[c][bits4][k - 1] * L.d.d_in / 4096.0);
 }
 
 template <int K, int CB>

@@ -324,25 +324,26 @@ static hipError_t launch_shape(Args& a, int rb, int nb_max, hipStream_t st) {
 }  // namespace gmid
 
 // Tile choice: rows rb and token blocks nb (tokens spread evenly over the n_tt token tiles) with the
-// least estimated time, rounds of workgroups (one per compute unit) times a tile's time on a
-// 4096-input layer: start and end, per plane and 16 rows (dequantization), per token block (X and the
-// products), fitted per shape (8-bit codes; us measured at one full round: 16 x 64 tokens 11.0 at k = 1
-// and 13.2 at k = 4, 32 x 32 8.9 and 14.5, 32 x 128 17.3 and 22.6, 48 x 64 13.5 and 22.1, 48 x 192 35.5 at
-// k = 4, 64 x 128 25.0 and 32.8).
+// least estimated time: a launch, and per round of workgroups (one per compute unit, a started round counts
+// whole) a tile's start and end, its stores (twice as long where d_out is not a multiple of four) and, for
+// 4096 inputs, dequantization per plane and 16 rows (4-bit codes: 0.75 of it) and X and the products per
+// token block. Fitted per shape to 2500 layers and token counts (d_out 200 .. 14000, d_in 200 .. 12000, 17 to
+// 3000 tokens, both code widths, inputs and outputs rotated): 5 % are measured below 0.9 or above 1.2 of the estimate.
 struct MidTile { int rb, nb_max, nb, n_tt; double us; };
 static MidTile mid_tile(const Layer& L, int k, int n, int rb = 0, int nb_max = 0) {   // rb > 0: that shape only
-  static const struct { int rb, nb; double start, plane, block; } shapes[9] = {
-      {1, 2, 5.3, 0.73, 1.0}, {1, 4, 6.0, 0.73, 1.0},  {2, 2, 4.8, 0.9, 1.15},
-      {2, 4, 5.6, 0.78, 1.2}, {2, 8, 5.0, 0.82, 1.4},  {3, 4, 5.2, 0.95, 1.35},
-      {3, 8, 8.0, 0.63, 1.42}, {3, 12, 9.0, 0.65, 1.53}, {4, 8, 8.0, 0.65, 1.75}};
-  const int ncu = L.n_cu > 0 ? L.n_cu : 256, blocks = (n + 15) / 16;
-  const double len = L.d.d_in / 4096.0;
+  static const struct { int rb, nb; double launch, start, store, plane, block; } shapes[9] = {
+      {1, 2, 1.6, 2.9, 0.23, 0.57, 1.19}, {1, 4, 1.8, 3.2, 0.17, 0.62, 1.27},  {2, 2, 1.6, 3.2, 0.14, 0.69, 0.96},
+      {2, 4, 1.3, 3.8, 0.14, 0.54, 1.15}, {2, 8, 1.1, 4.8, 0.14, 0.63, 1.16},  {3, 4, 1.5, 4.2, 0.13, 0.78, 0.93},
+      {3, 8, 1.8, 4.8, 0.11, 0.66, 1.52}, {3, 12, 1.8, 6.0, 0.10, 0.70, 1.57}, {4, 8, 1.7, 5.3, 0.10, 0.66, 1.66}};
+  const int ncu = L.n_cu > 0 ? L.n_cu : 256, blocks = (n + 15) / 16, odd = (L.d.d_out & 3) ? 2 : 1;
+  const double len = L.d.d_in / 4096.0, planes = L.d.code_bits == 4 ? 0.75 * k : k;
   MidTile best{};
   for (const auto& s : shapes) {
     if (rb > 0 && (s.rb != rb || s.nb != nb_max)) continue;
     const int tt = (blocks + s.nb - 1) / s.nb, b = (blocks + tt - 1) / tt;
     const long long wgs = (long long)((L.d.d_out + 16 * s.rb - 1) / (16 * s.rb)) * tt;
-    const double us = (double)((wgs + ncu - 1) / ncu) * (s.start + len * (s.plane * s.rb * k + s.block * b));
+    const double us = s.launch + (double)((wgs + ncu - 1) / ncu) *
+                                     (s.start + s.store * b * s.rb * odd + len * (s.plane * s.rb * planes + s.block * b));
     if (best.rb == 0 || us < best.us) best = {s.rb, s.nb, b, tt, us};
   }
   return best;

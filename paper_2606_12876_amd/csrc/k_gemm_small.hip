@@ -200,6 +200,13 @@ static hipError_t launch_small_k(const GemmSmallArgs& a, int code_bits, hipStrea
   return code_bits == 4 ? launch_small_cb<K, 4>(a, st) : launch_small_cb<K, 8>(a, st);
 }
 
+// Rounds of workgroups: a start, and for 4096 inputs the gathers per plane and 64 tokens, X and the products per
+// 16 tokens (17 to 144 tokens, 800 layers: 0.75 to 1.4 of the estimate).
+double gemm_small_us(const Layer& L, int k, int n_tokens) {
+  const int ncu = L.n_cu > 0 ? L.n_cu : 256, blocks = (n_tokens + 15) / 16;
+  return 1.7 + (((L.d.d_out + 15) / 16 + ncu - 1) / ncu) * (3.0 + L.d.d_in / 4096.0 * (0.71 * k * ((blocks + 3) / 4) + 2.29 * blocks));
+}
+
 hipError_t launch_gemm_small(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                              hipStream_t st) {
   GemmSmallArgs a{};

@@ -56,7 +56,8 @@ hipError_t launch_beam_search_weighted(const aqmb_desc& d, int k, int beam_width
 // as a filter; the same codes and errors bit for bit.
 hipError_t launch_beam_mma(const aqmb_desc& d, int k, int beam_width, const void* W, const uint16_t* codebooks,
                            const uint16_t* scales, const float* H, unsigned char* codes, float* errors, hipStream_t st);
-// Prefill GEMM tiled for small token counts (same arithmetic as launch_gemm).
+// Prefill GEMM tiled for small token counts (same arithmetic as launch_gemm), and its estimated time, k <= 4.
+double gemm_small_us(const Layer& L, int k, int n_tokens);
 hipError_t launch_gemm_small(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                              hipStream_t st);
 // Addresses in a token tile of the split-input GEMM: tokens t0 .. t0 + 16 nb - 1 of n, 32-bit byte
