@@ -473,6 +473,12 @@ uint32_t aqmb_test_gemm_mid_offset(int n, int t0, int nb, int d_in, int row, int
   return off < last ? off : last;
 }
 
+// For the tests: whether the two-pass GEMM's dense pass takes 256 x 256 tiles (-1: not a live layer).
+int aqmb_test_gemm_dense256(aqmb_layer_t layer, int n_tokens) {
+  Layer* L = (Layer*)layer;
+  return is_live(L) ? gemm_dense256(*L, n_tokens) : -1;
+}
+
 aqmb_status aqmb_gemm_workspace_bytes(aqmb_layer_t layer, int k, int n_tokens, size_t* bytes) {
   clear_error();
   Layer* L = (Layer*)layer;

@@ -581,7 +581,7 @@ static double gemm_rounds(const Layer& L, int n_tokens, int bm, int bn) {
 // these sizes every GEMM kernel starts its K walk at the first step: the staggered starts that keep
 // the column blocks of one round off the same X rows cost more than they save over several rounds
 // (8192 x 4096 x 4096, one pass, k = 1: 285 -> 269 us; 4096 tokens x 4096 x 11008: 381 -> 344 us).
-static bool gemm_dense256(const Layer& L, int n_tokens) {
+bool gemm_dense256(const Layer& L, int n_tokens) {
   if (gemm_tile(L, n_tokens, -1) != 0 || L.d.d_in > (1 << 20)) return false;
   const long long wg = (long long)((n_tokens + 255) / 256) * ((L.d.d_out + 127) / 128);
   if (wg < (L.n_cu > 0 ? L.n_cu : 256)) return false;

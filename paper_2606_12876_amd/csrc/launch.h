@@ -86,6 +86,7 @@ double gemm_large_us(const Layer& L, int k, int n_tokens);
 // Two-pass prefill GEMM (bit-identical to the 256 x 128 tiling): workspace bytes (0 where it does
 // not apply) and the launch (workspace of at least that many bytes, 256-byte aligned).
 size_t gemm_two_pass_bytes(const Layer& L, int k, int n_tokens);
+bool gemm_dense256(const Layer& L, int n_tokens);            // its dense pass takes 256 x 256 tiles
 hipError_t launch_gemm_two_pass(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
                                 void* workspace, hipStream_t st);
 

@@ -8,6 +8,8 @@ explicit bf16 weight rounding) pins both. Shapes: the full prefill workload at e
 codes, ragged rows / inputs / tokens with and without an XCD placement of the workgroups, both
 output dtypes, and the cases that fall back to aqmb_gemm.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -145,10 +147,10 @@ def test_quantlinear_takes_the_workspace_path():
 
 
 @pytest.mark.parametrize("d_out,d_in,n,ks", [
-    (4096, 512, 4096, (1, 2, 4)),      # one round of 256 x 256 tiles
-    (3900, 1000, 4000, (1, 3)),        # ragged rows (a 32-row block half empty), tokens and inputs
-    (8192, 64, 2048, (2,)),            # a single step
-    (5000, 136, 3400, (4,)),           # three steps, the last with one group; 14 token tiles (ragged XCD groups)
+    (4096, 1024, 4096, (1, 2, 4)),     # one round of 256 x 256 tiles
+    (3990, 1400, 4000, (1, 3)),        # ragged rows (a 32-row block partly empty), tokens and inputs
+    (8192, 64, 2048, (3,)),            # a single step
+    (4500, 136, 3400, (4,)),           # three steps, the last with one group; 14 token tiles (ragged XCD groups)
 ])
 def test_dense_256_tiles(d_out, d_in, n, ks):
     """The dense pass on 256 x 256 tiles: bit-identical to aqmb_gemm, and the oracle on sampled tokens."""
@@ -157,11 +159,10 @@ def test_dense_256_tiles(d_out, d_in, n, ks):
     X, Xv = to_dev(Xbits).view(torch.bfloat16), act_values(Xbits, "bf16")
     rows = np.r_[0:16, n // 2:n // 2 + 16, n - 16:n]
     with GpuLayer(L.codes, L.codebooks, L.scales) as gl:
+        assert A.lib.aqmb_test_gemm_dense256(ctypes.c_void_p(gl.handle), n) == 1
         for k in ks:
             nb = A.gemm_workspace_bytes(gl.handle, k, n)
-            if nb == 0:                                    # (k <= 2: only where two passes are estimated faster)
-                assert k < 3
-                continue
+            assert nb > 0, (d_out, d_in, n, k)
             ws = torch.full((nb // 2,), 0x7FC0, dtype=torch.int16, device="cuda")
             got = _run(gl, k, X, n, "bf16", ws)
             assert np.array_equal(got, _run(gl, k, X, n, "bf16", False)), (d_out, d_in, n, k)
