@@ -793,7 +793,7 @@ struct GemvMultiArgs {
   GemvMultiLayer L[AQMB_MAX_MULTI];
   const void* x;
   const void* zero_page;
-  int n_layers, total, d_in, S, y_dtype, nrep, cb_shift;  // total: row blocks of all layers
+  int total, d_in, S, y_dtype, nrep, cb_shift;            // total: row blocks of all layers
 };
 
 // The row blocks of all layers form one sequence, layer after layer, and a persistent workgroup per
@@ -903,11 +903,10 @@ static int cw_nrep(int K, int nb, int S, bool bf16, bool allow16 = false) {
 }
 static int cw_shift(int nrep) { return nrep == 16 ? 8 : nrep == 8 ? 7 : 6; }
 
-// LDS bytes with the paired layout (batch 1): (k + 1) / 2 regions plus the x tile; `sets`
-// replica sets (the multi-layer kernel's double buffering).
-static size_t cw_lds_paired(int K, int S, bool bf16, int sets = 1) {
+// LDS bytes with the paired layout (batch 1): (k + 1) / 2 regions plus the x tile.
+static size_t cw_lds_paired(int K, int S, bool bf16) {
   const size_t xt = cw::row_stride(S);
-  return (size_t)sets * ((K + 1) / 2) * kCwRegion + xt + (bf16 ? xt / 4 : 0);
+  return (size_t)((K + 1) / 2) * kCwRegion + xt + (bf16 ? xt / 4 : 0);
 }
 static size_t cw_budget(int nb, int sets = 1) {   // LDS left next to the row sums
   return 160 * 1024 - (size_t)sets * cw::kWaves * cw::kRows * 4 * nb - 512;
@@ -1101,7 +1100,6 @@ hipError_t launch_gemv_multi(const Layer* const* Ls, int n, int k, const void* x
   }
   a.x = x;
   a.zero_page = L0.zero_page();
-  a.n_layers = n;
   a.d_in = L0.d.d_in;
   a.S = L0.S;
   a.y_dtype = (int)y_dtype;
