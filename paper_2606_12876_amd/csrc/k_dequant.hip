@@ -417,7 +417,12 @@ __global__ __launch_bounds__(64 * NW) void dequant_kernel(const unsigned char* c
 //   tiles per compute unit (cold, against wave units: 4096 x 4096, k = 1..4, 8.6 8.7 9.0 9.7 against 10.2 9.6 10.3
 //   10.7, whose 4-row units read half lines), and 32 x 64 tiles once codes and output pass 148 MiB (14336 x
 //   4096, k = 6 / 8, 154 and 168 MiB: 34 / 37 against 37 / 41, k = 4, 140 MiB: 32 against 29; 28672 x 8192: 91 / 112
-//   at k = 1 / 4 against 100 / 122).
+//   at k = 1 / 4 against 100 / 122). From k = 3 on also where the wave units leave compute units idle (each wave one
+//   unit, workgroups filling less than 0.85 of their last round: 2116 x 8192, k = 4, cold, 14.0 against 16.8, 5120 x
+//   4096 14.1 against 16.4) or rows don't start on whole 128-byte lines and waves walk several units (11386 x 4912, k = 3,
+//   31.1 against 33.9; 5063 x 11272, k = 4, 37.5 against 40.5). Of 210 ragged layers at k = 3 and 4, units were more
+//   than 3 % slower than tiles on 86, with this rule on 12; mean 1.003 -> 0.985 of the tiles' time. At k >= 5 always
+//   (150 ragged layers: units 2.3 % slower on average, more than 3 % on 47).
 // - dequant_kernel for the rest, with at most as many workgroups as run at once, each wave walking its units
 //   with the grid's stride. Units of 8 rows (whole lines of codes), 8-wave workgroups where every wave gets a
 //   unit (8 per compute unit at k >= 3, 16 at k <= 2, where a unit is soon done), else 4-wave ones (4096 x 4096 to
@@ -449,7 +454,13 @@ static void launch_dequant_k(const Layer& L, void* W, hipStream_t st) {
         else tiles(dequant8_tile_kernel<OUT, K, 64, 64>, n_tiles(64, 64));
         return;
       }
-      if ((size_t)d_out * L.d.d_in * 2 + K * L.plane_bytes > ((size_t)148 << 20)) {
+      bool tile = K >= 5 || (size_t)d_out * L.d.d_in * 2 + K * L.plane_bytes > ((size_t)148 << 20);
+      const int wgs = (n_ct * ((d_out + 7) / 8) + 7) / 8;  // workgroups of wave units, one unit a wave
+      if (K >= 3 && wgs > ncu) {
+        const int per_cu = std::min<int>(160 * 1024 / (int)dequant_lds<CB, K, 8, 8>(), 4);
+        tile = tile || (wgs <= per_cu * ncu ? wgs < 0.85 * ncu * ((wgs + ncu - 1) / ncu) : L.d.d_in % 64 != 0);
+      }
+      if (tile) {
         tiles(dequant8_tile_kernel<OUT, K, 32, 64>, std::min(n_tiles(32, 64), 2 * ncu));
         return;
       }

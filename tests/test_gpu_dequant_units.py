@@ -65,6 +65,7 @@ def test_small_units(shape, M, B):
     ((32797, 16), 2, 4, (1, 2), ("bf16", "f32")),
     ((16397, 520), 2, 16, (1, 2), ("f16", "f32")),           # 16-bit codes: 8 rows, 8 waves at k = 1 to f32
     ((9473, 8232), 1, 8, (1,), ("bf16",)),                   # 159 MiB: output tiles
+    ((4099, 4104), 5, 8, (3, 5), ("f16",)),                  # output tiles: units that leave compute units idle, k >= 5
 ])
 def test_layers_of_many_units(shape, M, B, ks, dts):
     _check(shape, M, B, ks, dts)
