@@ -326,24 +326,28 @@ static hipError_t launch_shape(Args& a, int rb, int nb_max, hipStream_t st) {
 // Tile choice: rows rb and token blocks nb (tokens spread evenly over the n_tt token tiles) with the
 // least estimated time: a launch, and per round of workgroups (one per compute unit, a started round counts
 // whole) a tile's start and end, its stores (twice as long where d_out is not a multiple of four) and, for
-// 4096 inputs, dequantization per plane and 16 rows (4-bit codes: 0.75 of it) and X and the products per
-// token block. Fitted per shape to 2500 layers and token counts (d_out 200 .. 14000, d_in 200 .. 12000, 17 to
-// 3000 tokens, both code widths, inputs and outputs rotated): 5 % are measured below 0.9 or above 1.2 of the estimate.
+// 4096 inputs, dequantization per plane and 16 rows (8- and 4-bit codes) and X and the products per token block
+// (longer where the rows of X don't start on whole lines). Fitted per shape to 3500 layers and token
+// counts (d_out 200 .. 14000, d_in 200 .. 12000, 17 to 3000 tokens, both code widths, inputs and outputs
+// rotated): 10 % are measured below 0.9 or above 1.15 of the estimate.
 struct MidTile { int rb, nb_max, nb, n_tt; double us; };
 static MidTile mid_tile(const Layer& L, int k, int n, int rb = 0, int nb_max = 0) {   // rb > 0: that shape only
-  static const struct { int rb, nb; double launch, start, store, plane, block; } shapes[9] = {
-      {1, 2, 1.6, 2.9, 0.23, 0.57, 1.19}, {1, 4, 1.8, 3.2, 0.17, 0.62, 1.27},  {2, 2, 1.6, 3.2, 0.14, 0.69, 0.96},
-      {2, 4, 1.3, 3.8, 0.14, 0.54, 1.15}, {2, 8, 1.1, 4.8, 0.14, 0.63, 1.16},  {3, 4, 1.5, 4.2, 0.13, 0.78, 0.93},
-      {3, 8, 1.8, 4.8, 0.11, 0.66, 1.52}, {3, 12, 1.8, 6.0, 0.10, 0.70, 1.57}, {4, 8, 1.7, 5.3, 0.10, 0.66, 1.66}};
+  static const struct { int rb, nb; double launch, start, store, plane8, plane4, block, ragged; } shapes[9] = {
+      {1, 2, 1.68, 2.63, 0.28, 0.61, 0.43, 1.05, 0.15}, {1, 4, 1.85, 3.10, 0.18, 0.62, 0.43, 1.12, 0.20},
+      {2, 2, 1.59, 3.05, 0.16, 0.72, 0.55, 0.83, 0.11}, {2, 4, 1.50, 3.54, 0.15, 0.56, 0.45, 0.97, 0.17},
+      {2, 8, 1.30, 4.65, 0.15, 0.67, 0.51, 0.92, 0.24}, {3, 4, 1.50, 4.03, 0.15, 0.77, 0.63, 0.82, 0.06},
+      {3, 8, 1.61, 4.77, 0.11, 0.66, 0.57, 1.43, 0.10}, {3, 12, 1.75, 5.97, 0.10, 0.69, 0.59, 1.47, 0.13},
+      {4, 8, 1.63, 5.19, 0.10, 0.67, 0.58, 1.54, 0.09}};
   const int ncu = L.n_cu > 0 ? L.n_cu : 256, blocks = (n + 15) / 16, odd = (L.d.d_out & 3) ? 2 : 1;
-  const double len = L.d.d_in / 4096.0, planes = L.d.code_bits == 4 ? 0.75 * k : k;
+  const double len = L.d.d_in / 4096.0;
   MidTile best{};
   for (const auto& s : shapes) {
     if (rb > 0 && (s.rb != rb || s.nb != nb_max)) continue;
     const int tt = (blocks + s.nb - 1) / s.nb, b = (blocks + tt - 1) / tt;
     const long long wgs = (long long)((L.d.d_out + 16 * s.rb - 1) / (16 * s.rb)) * tt;
+    const double plane = L.d.code_bits == 4 ? s.plane4 : s.plane8, block = s.block + (L.d.d_in % 64 ? s.ragged : 0.0);
     const double us = s.launch + (double)((wgs + ncu - 1) / ncu) *
-                                     (s.start + s.store * b * s.rb * odd + len * (s.plane * s.rb * planes + s.block * b));
+                                     (s.start + s.store * b * s.rb * odd + len * (plane * s.rb * k + block * b));
     if (best.rb == 0 || us < best.us) best = {s.rb, s.nb, b, tt, us};
   }
   return best;
