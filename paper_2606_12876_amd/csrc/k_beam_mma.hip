@@ -838,32 +838,35 @@ __global__ __launch_bounds__(64 * kWaves) void beam_mma_kernel(Args a) {
     // is not a number no candidate has one, and every stage's entries are missing.
     uint32_t taint = 0, done, hopeless;
     {
-      const Tuple t = load_tuple<WT>(M, tb, 0, lane & 31, 0);
       const uint4 w = M.w[lane & 31];
       const float s = M.s[lane & 31];
       const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-      bool nan = false, inf = false, zero = s == 0.f && fabsf(t.base) < 1e30f;
+      bool nan = false, inf = false;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const uint32_t lo = u[q] & 0x7FFFu, hi = (u[q] >> 16) & 0x7FFFu;
         nan = nan || lo > 0x7C00u || hi > 0x7C00u;
         inf = inf || lo == 0x7C00u || hi == 0x7C00u;
       }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) zero = zero && fabsf(t.v[i]) < 1e30f;
-      for (int m = 0; m < a.k; ++m) zero = zero && !info[m].bad;
-      zero = zero && !inf && !nan;
       hopeless = (uint32_t)__ballot(nan || inf || s == 0.f || !(fabsf(s) < 1e30f));
-      done = (uint32_t)__ballot(zero || nan);
-      if (lane < 32 && (zero || nan)) {
-        const int m = a.k - 1;
-        const float ginv = pow2f(-info[m].g);
-        const uint32_t c = nan ? 0xFFu : 0u;
-        M.st[lane][0] = make_uint2(m < 4 ? c << (8 * m) : 0u, m < 4 ? 0u : c << (8 * (m - 4)));
-        M.oute[lane] = nan ? __builtin_inff()
-                           : exact_error<WT>(t.v, t.base, books[m * 256], s, -s * ginv, ginv, WT ? Qs[m * 256] : 0.f);
+      done = 0;
+      if (hopeless) {                                // (uniform)
+        const Tuple t = load_tuple<WT>(M, tb, 0, lane & 31, 0);
+        bool zero = s == 0.f && fabsf(t.base) < 1e30f && !inf && !nan;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) zero = zero && fabsf(t.v[i]) < 1e30f;
+        for (int m = 0; m < a.k; ++m) zero = zero && !info[m].bad;
+        done = (uint32_t)__ballot(zero || nan);
+        if (lane < 32 && (zero || nan)) {
+          const int m = a.k - 1;
+          const float ginv = pow2f(-info[m].g);
+          const uint32_t c = nan ? 0xFFu : 0u;
+          M.st[lane][0] = make_uint2(m < 4 ? c << (8 * m) : 0u, m < 4 ? 0u : c << (8 * (m - 4)));
+          M.oute[lane] = nan ? __builtin_inff()
+                             : exact_error<WT>(t.v, t.base, books[m * 256], s, -s * ginv, ginv, WT ? Qs[m * 256] : 0.f);
+        }
+        wave_sync();
       }
-      wave_sync();
     }
     for (int m = 0; m < a.k && done != ~0u; ++m) {
       const bool last = m == a.k - 1;
