@@ -26,10 +26,10 @@
 // key of every kept tuple) stays in LDS.
 //
 // Measured (4096 x 4096, k = 4, beam 8): 11.3 ms for the lane-per-group search of k_beam.hip, 2.48 ms
-// here; data-aware (2000 x 2304, k = 3, beam 5): 1256 -> 512 us. The bound is still vector issue: a
-// pass (8192 candidates) takes about 750 vector instructions, 144 of them the minima and compares
-// of every candidate, 170 the threshold, 115 its columns' preparation, 170 the exact errors; the
-// eight MFMAs hide under them.
+// here; data-aware (2000 x 2304, k = 3, beam 5): 1256 -> 512 us. The bound is still vector issue, busy 70 % of
+// the time by the counters (the matrix cores 7 %): a pass (8192 candidates) takes 636 vector
+// instructions. By reading, 144 of them are the minima and compares of every candidate, about 170 each
+// the threshold and the exact errors, 115 its columns' preparation; the eight MFMAs hide under them.
 #include "device.h"
 #include "launch.h"
 
