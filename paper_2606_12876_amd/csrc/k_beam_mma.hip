@@ -840,15 +840,14 @@ __global__ __launch_bounds__(64 * kWaves) void beam_mma_kernel(Args a) {
     {
       const uint4 w = M.w[lane & 31];
       const float s = M.s[lane & 31];
-      const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-      bool nan = false, inf = false;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t lo = u[q] & 0x7FFFu, hi = (u[q] >> 16) & 0x7FFFu;
-        nan = nan || lo > 0x7C00u || hi > 0x7C00u;
-        inf = inf || lo == 0x7C00u || hi == 0x7C00u;
-      }
-      hopeless = (uint32_t)__ballot(nan || inf || s == 0.f || !(fabsf(s) < 1e30f));
+      typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+      const u16x2_t mask = {0x7FFF, 0x7FFF};
+      auto mag = [&](uint32_t u) { return __builtin_bit_cast(u16x2_t, u) & mask; };
+      const u16x2_t top2 = __builtin_elementwise_max(__builtin_elementwise_max(mag(w.x), mag(w.y)),
+                                                     __builtin_elementwise_max(mag(w.z), mag(w.w)));
+      const uint32_t top = top2[0] > top2[1] ? top2[0] : top2[1];   // the largest magnitude's bits
+      const bool nan = top > 0x7C00u, inf = top == 0x7C00u;
+      hopeless = (uint32_t)__ballot(top >= 0x7C00u || s == 0.f || !(fabsf(s) < 1e30f));
       done = 0;
       if (hopeless) {                                // (uniform)
         const Tuple t = load_tuple<WT>(M, tb, 0, lane & 31, 0);
