@@ -212,10 +212,10 @@ static aqmb_status launch_gemv_kernel(const Layer& L, int k, const void* x, aqmb
 // large-tile kernel with the tile shape that needs the fewest rounds of workgroups; instead of either, from
 // 17 tokens and up to k = 4, the split-input kernel (k_gemm_mid.hip) where its estimated time is well below
 // theirs (4096 x 4096, k = 4, large tiles or 16-row tiling against it: 23.0 / 13.3 us at 64 tokens, 52.1 / 20.1 at
-// 150, 76.1 / 61.1 at 1024, 89.6 / 91.3 at 1500, where the large tiles stay). The margins are the estimates'
-// errors: on 2541 layers and token counts that the estimates were not fitted to, 4 calls are slower than without
-// that kernel (0.94 to 0.98 times the speed), and the mean speed is 1.47 times theirs on ragged layers, 1.63 on
-// aligned ones, of 1.49 and 1.66 with every choice right. (With 0.95 on estimates made on few shapes one call
+// 150, 76.1 / 61.1 at 1024, 89.6 / 91.3 at 1500, where the large tiles stay). The margin is the estimates'
+// errors: on 2541 layers and token counts that the estimates were not fitted to, 3 calls are slower than without
+// that kernel (0.95 to 0.98 times the speed), and the mean speed is 1.53 times theirs, of 1.54 with every
+// choice right. (With 0.95 on estimates made on few shapes one call
 // in ten was slower, down to 0.57.) Never where aqmb_gemm_ws has a
 // two-pass path: that is bit-identical to the 256 x 128 tiling.
 constexpr int kGemmSmallMax = 144;   // tokens: the 16-row tiling re-gathers per 64 tokens; measured break-even with 128 x 64 tiles near 150
@@ -223,7 +223,7 @@ static bool gemm_takes_mid(const Layer& L, int k, int n_tokens) {
   if (n_tokens <= 16 || gemm_two_pass_bytes(L, k, n_tokens) != 0) return false;
   const double mid = gemm_mid_us(L, k, n_tokens);
   if (mid < 0) return false;
-  return mid < (n_tokens <= kGemmSmallMax ? 0.85 * gemm_small_us(L, k, n_tokens) : 0.9 * gemm_large_us(L, k, n_tokens));
+  return mid < 0.9 * (n_tokens <= kGemmSmallMax ? gemm_small_us(L, k, n_tokens) : gemm_large_us(L, k, n_tokens));
 }
 
 // k must name resident planes.

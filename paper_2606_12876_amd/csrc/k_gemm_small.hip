@@ -200,11 +200,14 @@ static hipError_t launch_small_k(const GemmSmallArgs& a, int code_bits, hipStrea
   return code_bits == 4 ? launch_small_cb<K, 4>(a, st) : launch_small_cb<K, 8>(a, st);
 }
 
-// Rounds of workgroups: a start, and for 4096 inputs the gathers per plane and 64 tokens, X and the products per
-// 16 tokens (17 to 144 tokens, 800 layers: 0.75 to 1.4 of the estimate).
+// A launch, then in proportion to the workgroups (row blocks x passes of up to 64 tokens) above one per compute
+// unit a start and, for 4096 inputs, the gathers per plane and X and the products of a pass by its 16-token blocks
+// (17 to 144 tokens, 2600 layers and token counts: 0.83 to 1.45 of the estimate, the long ones on tall layers).
 double gemm_small_us(const Layer& L, int k, int n_tokens) {
-  const int ncu = L.n_cu > 0 ? L.n_cu : 256, blocks = (n_tokens + 15) / 16;
-  return 1.7 + (((L.d.d_out + 15) / 16 + ncu - 1) / ncu) * (3.0 + L.d.d_in / 4096.0 * (0.71 * k * ((blocks + 3) / 4) + 2.29 * blocks));
+  const int blocks = (n_tokens + 15) / 16, passes = (blocks + 3) / 4, per = blocks < 4 ? blocks : 4;
+  const double wgs = (double)((L.d.d_out + 15) / 16) * passes / (L.n_cu > 0 ? L.n_cu : 256);
+  return 1.0 + (wgs > 1.0 ? wgs : 1.0) * (4.0 + L.d.d_in / 4096.0 * ((L.d.code_bits == 4 ? 1.19 : 1.42) * k +
+                                                                  (per <= 2 ? 2.43 : per == 3 ? 7.13 : 9.33)));
 }
 
 hipError_t launch_gemm_small(const Layer& L, int k, const void* X, int n_tokens, void* Y, aqmb_dtype y_dtype,
